@@ -818,15 +818,24 @@ __host__ __device__ __forceinline__ void jets_fix_node(const Params<R>& P, S* __
   if (y == 0 || y == ny - 1) {
     const int cin = y == 0 ? 1 : -1;                 // c_y of the directions entering
     const int64_t inner = row + (int64_t)cin * nx;   // (0, y + cin, z)
+    // every value is read before the first is written: copied one by one, each load
+    // waits for the store before it (the compiler cannot know that the slots read are
+    // never written): 13.0 -> 8.9 us on 200 x 400 with M = 4
+    S in[L][9];
 #pragma unroll
     for (int l = 0; l < L; ++l)
 #pragma unroll
-      for (int i = 0; i < Q; ++i) {
-        if (cy(i) != cin) continue;
-        int xs = x - cx(i);
+      for (int k = 0; k < 9; ++k) {
+        const int ci = k / 3 - 1, i = 9 * (k / 3) + 3 * (cin + 1) + k % 3;   // c_x and direction
+        int xs = x - ci;
         xs = xs < 0 ? 0 : (xs >= nx ? nx - 1 : xs);
-        dst[(size_t)(l * Q + i) * n + node] = dst[(size_t)(l * Q + i) * n + inner + xs + cx(i)];
+        in[l][k] = dst[(size_t)(l * Q + i) * n + inner + xs + ci];
       }
+#pragma unroll
+    for (int l = 0; l < L; ++l)
+#pragma unroll
+      for (int k = 0; k < 9; ++k)
+        dst[(size_t)(l * Q + 9 * (k / 3) + 3 * (cin + 1) + k % 3) * n + node] = in[l][k];
   }
   if (nozzle_row(P, y) && (x == 0 || x == nx - 1)) {
 #pragma unroll
