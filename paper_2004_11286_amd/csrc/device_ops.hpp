@@ -59,13 +59,15 @@ __device__ inline int16_t fma_sr_i16(float a, float b, uint32_t k8, float& y)
 // probability equal to the dropped fraction, so the result is unbiased (its
 // expectation is x, to 2^-24 of a unit in the last place). The conversion of
 // the cut value is exact for every x in FP32's normal range.
-__device__ inline float cvt_sr_f32(double x, uint32_t rnd)
+__device__ inline double sr_cut_f32(double x, uint32_t rnd)
 {
   uint64_t b = (uint64_t)__double_as_longlong(x);
   b += (uint64_t)(rnd >> 8) << 5;
   b &= ~(((uint64_t)1 << 29) - 1);
-  return (float)__longlong_as_double((long long)b);
+  return __longlong_as_double((long long)b);
 }
+
+__device__ inline float cvt_sr_f32(double x, uint32_t rnd) { return (float)sr_cut_f32(x, rnd); }
 
 // Buffer accesses to one direction's array of a lattice (n values from base). The
 // resource (base address and byte size, in scalar registers) is the same for the
@@ -92,19 +94,26 @@ __device__ __forceinline__ T buf_load(const T* base, uint32_t n, uint32_t idx)
   else return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b16(r, off, 0, AUX));
 }
 
+// Store at a per-lane byte offset plus a uniform one of a range of `bytes` bytes from base.
+template <typename T, int AUX = BUF_CACHED>
+__device__ __forceinline__ void buf_store_at(T* base, uint32_t bytes, uint32_t off, T v,
+                                             uint32_t soff = 0)
+{
+  const __amdgpu_buffer_rsrc_t r = buf_rsrc(base, bytes);
+  if constexpr (sizeof(T) == 8) {
+    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, off, soff, AUX);
+  } else if constexpr (sizeof(T) == 4) {
+    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), r, off, soff, AUX);
+  } else {
+    __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(uint16_t, v), r, off, soff, AUX);
+  }
+}
+
 template <typename T, int AUX = BUF_CACHED>
 __device__ __forceinline__ void buf_store(T* base, uint32_t n, uint32_t idx, T v)
 {
-  const __amdgpu_buffer_rsrc_t r = buf_rsrc(base, n * (uint32_t)sizeof(T));
-  const uint32_t off = idx * (uint32_t)sizeof(T);
-  if constexpr (sizeof(T) == 8) {
-    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, off, 0, AUX);
-  } else if constexpr (sizeof(T) == 4) {
-    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), r, off, 0, AUX);
-  } else {
-    __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(uint16_t, v), r, off, 0, AUX);
-  }
+  buf_store_at<T, AUX>(base, n * (uint32_t)sizeof(T), idx * (uint32_t)sizeof(T), v);
 }
 
 // Load of a value that is read once and not again soon (the populations a

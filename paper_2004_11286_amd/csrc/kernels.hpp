@@ -165,29 +165,55 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(collide_p
 // The two-read step: the moments pass also collides and streams the species
 // lattices (k_state_species); the second pass collides and streams the momentum
 // and energy lattices (k_collide_fg). The two write disjoint lattices of dst.
+// Waves per SIMD of k_state_species and k_collide_fg. The upper bound matters as much
+// as the lower one: below it the compiler's scheduler gives up loads in flight to reach
+// a register count that lets one more wave in, and puts a wait after each load (the
+// fixed-point k_collide_fg on 190 x 164 x 156 nodes at two waves: 599 us without the
+// bound, 447 us with it). 16-bit state passes
+// keep their registers low by themselves (four waves) and are left free.
+// Three stored species or more in FP64 arithmetic, and two with FP64 storage too, take
+// one wave and the whole register file (four species at two waves spill 288 bytes per
+// lane).
+template <typename S, typename R, int M, int V, bool WEAK>
+constexpr int state_waves()
+{
+  constexpr int NS = Lat<M, WEAK>::NS;
+  if (sizeof(S) == 2) return moment_waves<M, V>();
+  const bool two = M == 2 || sizeof(R) == 4 || (NS == 2 && sizeof(S) == 4);
+  return V == 0 ? (two ? 2 : 1) : (M == 2 ? 3 : (two ? 1 : 2));
+}
+template <typename S, typename R, int M, int V, bool WEAK>
+constexpr int state_waves_max() { return sizeof(S) == 2 ? 8 : state_waves<S, R, M, V, WEAK>(); }
+
 template <typename S, typename R, typename Rec, int M, int W, int V, bool WEAK>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(moment_waves<M, V>()))) void k_state_species(
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(state_waves<S, R, M, V, WEAK>(), state_waves_max<S, R, M, V, WEAK>()))) void k_state_species(
     const Params<R>* __restrict__ P, Launch Ln, const S* __restrict__ src, S* __restrict__ dst, Rec* __restrict__ rec,
     StepNo sn)
 {
   const Where w = locate(Ln);
   const Params<R>& Pt = P[w.t];
   static_assert(RecLayout<M, WEAK, false>::FIELDS >= REC2_FIELDS, "the two-read record fits the record buffer");
+  constexpr bool LDS = hold_mode<S, R, M, WEAK>() == HOLD_LDS;
+  __shared__ S held[LDS ? Lat<M, WEAK>::NS * Q * BLOCK : 1];     // [value][thread], each thread its own column
   if (w.node < Pt.n) {
     const size_t po = pop_stride<M, WEAK>() * w.base;
-    state_species_node<S, R, Rec, M, W, WEAK>(Pt, src + po, dst + po,
-                                              rec + (size_t)RecLayout<M, WEAK, false>::FIELDS * w.base, w.node,
-                                              step_of(sn));
+    state_species_node<S, R, Rec, M, W, WEAK, BLOCK>(Pt, src + po, dst + po,
+                                                     rec + (size_t)RecLayout<M, WEAK, false>::FIELDS * w.base, w.node,
+                                                     step_of(sn), held + (LDS ? threadIdx.x : 0));
   }
 }
 
 // Occupancy targets of k_collide_fg: two waves per SIMD (variant 0; about 230
 // registers), or no bound on the registers (variant 1: one wave per SIMD).
+// 16-bit floating point fits three waves by itself and is left free above (131 x 97 x
+// 89: 96 us, held to two waves 103 us).
 template <int V>
 constexpr int collide_fg_waves() { return V == 0 ? 2 : 1; }
+template <typename S, int V>
+constexpr int collide_fg_waves_max() { return sizeof(S) == 2 && !is_fixed16<S>() ? 8 : collide_fg_waves<V>(); }
 
 template <typename S, typename R, typename Rec, int M, int W, int V, bool WEAK>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(collide_fg_waves<V>()))) void k_collide_fg(
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(collide_fg_waves<V>(), collide_fg_waves_max<S, V>()))) void k_collide_fg(
     const Params<R>* __restrict__ P, Launch Ln, const S* __restrict__ src, S* __restrict__ dst,
     const Rec* __restrict__ rec, const Rec* __restrict__ G, StepNo sn)
 {

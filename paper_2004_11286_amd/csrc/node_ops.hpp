@@ -288,6 +288,11 @@ __host__ __device__ __forceinline__ Nbr neighbours(const Params<R>& P, int64_t n
 // zero-gradient outlets at both y ends (the jets' outlets); otherwise y is periodic.
 enum { BC_PERIODIC = 0, BC_WALLS = 1, BC_OPEN = 2, BC_JETS = 3, BC_YSLIP = 4, BC_YOUT = 8 };
 __host__ __device__ constexpr int xbc(int BC) { return BC & 3; }
+// Some boundary reflects a population into another direction.
+__host__ __device__ constexpr bool reflecting(int BC)
+{
+  return xbc(BC) == BC_WALLS || xbc(BC) == BC_JETS || (BC & BC_YSLIP) != 0;
+}
 
 // A nozzle row of the opposed jets.
 template <typename R>
@@ -355,15 +360,27 @@ __host__ __device__ __forceinline__ void species_present(const Params<R>& P, con
   for (int a = 0; a < M; ++a) present[a] = rho_a[a] > P.absent_tol * rho || rho_a[a] < -P.absent_tol * rho;
 }
 
-template <typename R, int M>
+// The kernels whose register allocation is tight must not branch on a lane's state: the
+// compiler (clang of ROCm 7.2) may put the copies it splits a live range with at the start
+// of a join block, before the lanes switched off are switched on again, and those lanes
+// then keep a stale value. (The four-species FP64 state pass at one wave per SIMD did so
+// after the branches on absent species: the populations of nodes with an absent species
+// came out 1e-7 off.) So absence enters as a factor 1 or 0 here (MASK: FP64 and FP32
+// storage), and the streaming selects its offsets with masks (push_all).
+template <typename R, int M, bool MASK>
 __host__ __device__ __forceinline__ void friction_matrix(const Params<R>& P, const Mix<R, M>& s, R Pk,
                                                 const bool present[M], R K[M][M])
 {
+  R in[M];
+#pragma unroll
+  for (int a = 0; a < M; ++a) in[a] = present[a] ? R(1) : R(0);
 #pragma unroll
   for (int a = 0; a < M; ++a)
 #pragma unroll
-    for (int c = 0; c < M; ++c)
-      K[a][c] = (present[a] && present[c]) ? Pk * s.X[a] * s.X[c] * P.invD[a][c] : R(0);
+    for (int c = 0; c < M; ++c) {
+      if constexpr (MASK) K[a][c] = Pk * s.X[a] * s.X[c] * P.invD[a][c] * (in[a] * in[c]);
+      else K[a][c] = (present[a] && present[c]) ? Pk * s.X[a] * s.X[c] * P.invD[a][c] : R(0);
+    }
 }
 
 template <typename R, int M>
@@ -500,7 +517,7 @@ __host__ __device__ __forceinline__ void state_node(const Params<double>& P, con
   species_present<D, M>(P, s.rho_a, s.rho, present);
   D K[M][M], V[M][3];
   if constexpr (CVT) Pk *= inv_diffusivity_factor<D>(P, s.T);   // K_ab = P X_a X_b / D_ab(T)
-  friction_matrix<D, M>(P, s, Pk, present, K);
+  friction_matrix<D, M, sizeof(S) >= 4>(P, s, Pk, present, K);
   diffusion_velocities<D, M>(s, present, K, js, us, V);
   const D theta = s.Rg * s.T;
   D mu_mix, lam_mix;
@@ -714,14 +731,31 @@ __host__ __device__ __forceinline__ S to_store(const Params<R>& P, int l, int i,
     rng.ymin = __builtin_elementwise_minimum(rng.ymin, y);
     return v;
   } else {
-    return Store<S, R>::cvt(dev * P.scale[l], rng.next());
+    return Store<S, R>::cvt(sizeof(S) >= 4 ? dev : dev * P.scale[l], rng.next());
   }
 }
 
+// FP64 and FP32 storage have unit scales (scale_for): no multiplication there.
 template <typename S, typename R>
 __host__ __device__ __forceinline__ R from_store(const Params<R>& P, int l, int i, S v)
 {
-  return R(v) * dec_scale<S, R>(P, l, i);
+  if constexpr (sizeof(S) >= 4) return R(v);
+  else return R(v) * dec_scale<S, R>(P, l, i);
+}
+
+// Round to storage and return the stored value decoded again. FP32 storage of FP64
+// arithmetic has that value as an FP64 number before the (exact) conversion.
+template <typename S, typename R>
+__host__ __device__ __forceinline__ R round_store(const Params<R>& P, int l, int i, R dev, Rng& rng, S& v)
+{
+  if constexpr (std::is_same<S, float>::value && std::is_same<R, double>::value) {
+    const double x = sr_cut_f32(dev, rng.next());
+    v = (float)x;
+    return x;
+  } else {
+    v = to_store<S, R>(P, l, i, dev, rng);
+    return from_store<S, R>(P, l, i, v);
+  }
 }
 
 // Fixed-point storage: after a lattice's stores, set bit 0 of the context's range
@@ -744,42 +778,77 @@ __host__ __device__ __forceinline__ void range_check(const Params<R>& P, const R
   }
 }
 
-// Streaming: write the post-collision value of direction i to the neighbour
-// x + c_i of the other buffer, or bounce it back at an x wall. Open ends stream
-// as periodic here; open_fix_node then rewrites what enters the two boundary
-// planes (the wrapped values are exactly the ones an open end drops).
+// Streaming: write the post-collision values of one lattice to the neighbours x + c_i
+// of the other buffer. Half-way bounce-back x walls return a value into the opposite
+// direction of the node itself; a free-slip y wall reflects it specularly (c_y
+// reversed) at its own y, and so do, in x, the walls beside the jets' nozzles, decided
+// by the destination row (through a nozzle it wraps into a slot that jets_fix_node
+// overwrites with the inlet equilibrium). Open ends and outlets stream as periodic
+// here; open_fix_node and jets_fix_node then rewrite what enters there (the wrapped
+// values are exactly the ones such an end drops). Cached stores: the shifted stores of
+// a wavefront merge into whole lines in the cache.
+//
+// Without reflecting boundaries each direction's array has its own buffer resource.
+// With them a lane at a wall stores into another direction's array: one resource over
+// the whole lattice (Q n values) and a per-lane byte offset serve every lane with one
+// store per direction. Through the directions' own resources the reflected lanes needed
+// a branch and a second, global store in each of the 18 directions that cross a wall;
+// in the tubes nearly every wavefront holds a wall node (512 tubes of 32..256 x 16 x 16,
+// M = 3, FP32: k_collide_fg 5.31 -> 2.19 ms). The offsets need Q n values below 2^32
+// bytes; larger tubes store through 64-bit addresses.
 template <typename S, typename R, int BC>
-__host__ __device__ __forceinline__ void push(const Params<R>& P, S* __restrict__ dst, const Nbr& b, int l, int i,
-                                     int64_t node, S v)
+__host__ __device__ __forceinline__ void push_all(const Params<R>& P, S* __restrict__ dst, const Nbr& b, int l,
+                                                  int64_t node, const S (&v)[Q])
 {
-  const size_t n = (size_t)P.n;
-  const bool xout = (cx(i) < 0 && b.lo) || (cx(i) > 0 && b.hi);
-  const bool yout = (cy(i) < 0 && b.ylo) || (cy(i) > 0 && b.yhi);
-  // destination direction j and node d (a 32-bit index, as every node index here)
-  int j = i;
-  uint32_t d = b.x[cx(i) + 1] + b.y[cy(i) + 1] + b.z[cz(i) + 1];
-  if (xbc(BC) == BC_WALLS && xout) {
-    j = opp(i);                                       // half-way bounce-back
-    d = (uint32_t)node;
-  } else if (xbc(BC) == BC_JETS && xout && !((BC & BC_YOUT) && yout) &&
-             !nozzle_row(P, (int)b.yy + cy(i))) {
-    // beside a nozzle: free-slip wall, specular reflection (c_x reversed) at the
-    // node's own x; through a nozzle the value wraps into a slot that
-    // jets_fix_node overwrites with the inlet equilibrium
-    j = i - 18 * cx(i);
-    d = b.x[1] + b.y[cy(i) + 1] + b.z[cz(i) + 1];
-  } else if ((BC & BC_YSLIP) && yout) {
-    // free-slip y wall: specular reflection (c_y reversed) at the node's own y
-    j = i - 6 * cy(i);
-    d = b.x[cx(i) + 1] + b.y[1] + b.z[cz(i) + 1];
+  if constexpr (!reflecting(BC)) {
+    const size_t n = (size_t)P.n;
+#pragma unroll
+    for (int i = 0; i < Q; ++i)
+      buf_store<S>(dst + (size_t)(l * Q + i) * n, (uint32_t)n, b.x[cx(i) + 1] + b.y[cy(i) + 1] + b.z[cz(i) + 1], v[i]);
+  } else {
+    constexpr bool XREF = xbc(BC) == BC_WALLS || xbc(BC) == BC_JETS;
+    S* lat = dst + (size_t)l * Q * P.n;
+    // all ones in the lanes that touch an end: the offsets are selected without branches
+    auto mask = [](bool c) -> uint32_t { return c ? ~0u : 0u; };
+    const uint32_t xm[2] = {mask(b.lo), mask(b.hi)}, ym[2] = {mask(b.ylo), mask(b.yhi)};
+    uint32_t wall[3] = {~0u, ~0u, ~0u};              // jets: a push to row y + c meets a wall row
+    if constexpr (xbc(BC) == BC_JETS) {
+#pragma unroll
+      for (int c = -1; c <= 1; ++c) {
+        wall[c + 1] = ~mask(nozzle_row(P, (int)b.yy + c));
+        if (c) wall[c + 1] &= ~ym[(c + 1) / 2];      // beyond an outlet: not reflected
+      }
+    }
+    // offset of direction i in units of which a node is u and a direction's array nu
+    auto offset = [&](int i, auto u, auto nu) {
+      using U = decltype(u);
+      const int c = cx(i), e = cy(i);
+      auto sel = [](uint32_t m, U a, U o) -> U {
+        const U mm = (U)(int64_t)(int32_t)m;
+        return (a & mm) | (o & ~mm);
+      };
+      const U x = b.x[c + 1] * u, y = b.y[e + 1] * u, z = b.z[cz(i) + 1] * u;
+      U o = x + y + z + (U)i * nu;
+      if ((BC & BC_YSLIP) && e) o = sel(ym[(e + 1) / 2], x + b.y[1] * u + z + (U)(i - 6 * e) * nu, o);
+      if (XREF && c) {
+        if constexpr (xbc(BC) == BC_WALLS) o = sel(xm[(c + 1) / 2], (U)(uint32_t)node * u + (U)opp(i) * nu, o);
+        else o = sel(xm[(c + 1) / 2] & wall[e + 1], b.x[1] * u + y + z + (U)(i - 18 * c) * nu, o);
+      }
+      return o;
+    };
+    if ((uint64_t)P.n * (Q * sizeof(S)) < ((uint64_t)1 << 32)) {
+      const uint32_t u = (uint32_t)sizeof(S), nu = (uint32_t)P.n * u;
+#pragma unroll
+      for (int i = 0; i < Q; ++i) {
+        if ((XREF && cx(i)) || ((BC & BC_YSLIP) && cy(i))) buf_store_at<S>(lat, Q * nu, offset(i, u, nu), v[i]);
+        else
+          buf_store_at<S>(lat, Q * nu, (b.x[cx(i) + 1] + b.y[cy(i) + 1] + b.z[cz(i) + 1]) * u, v[i], (uint32_t)i * nu);
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < Q; ++i) lat[offset(i, (uint64_t)1, (uint64_t)P.n)] = v[i];
+    }
   }
-  // cached stores: the shifted pushes of a wavefront merge into whole lines in the
-  // cache. The buffer resource must be the same for every lane of the wavefront,
-  // so the buffer store takes only values that keep their direction; a value
-  // reflected into another direction (which lanes do depends on their position)
-  // takes a global store. A wavefront away from every wall skips that branch.
-  if (j == i) buf_store<S>(dst + (size_t)(l * Q + i) * n, (uint32_t)n, d, v);
-  else dst[(size_t)(l * Q + j) * n + d] = v;
 }
 
 // Load the Q stored values of one lattice of a node into v (lat: the lattice's
@@ -890,6 +959,12 @@ __host__ __device__ __forceinline__ void open_fix_node(const Params<R>& P, S* __
 template <typename S>
 using SrcF = typename std::conditional<sizeof(S) == 8, double, float>::type;
 
+// FP64 and FP32 storage evaluate the collisions in the factored forms below; 16-bit
+// storage keeps the direction-by-direction forms, because its stochastic rounding
+// turns a difference in the last FP32 bit into another rounding of a stored value.
+template <typename S>
+constexpr bool factored() { return sizeof(S) >= 4; }
+
 // Face pairs (c = +e_k, -e_k) of the velocity set, k = x, y, z.
 constexpr int face_plus(int k) { return k == 0 ? 22 : (k == 1 ? 16 : 14); }
 
@@ -907,23 +982,103 @@ __host__ __device__ __forceinline__ void restore_faces(const Params<R>& P, int l
     const int ip = face_plus(k), im = 26 - ip;
     const R sum = face[ip] + face[im];
     const R diff = t1[k] - s1[k];        // required stored value of ip minus that of im
-    v[ip] = to_store<S, R>(P, l, ip, R(0.5) * (sum + diff), rng);
-    v[im] = to_store<S, R>(P, l, im, R(0.5) * (sum - diff), rng);
-    s0 += from_store<S, R>(P, l, ip, v[ip]) + from_store<S, R>(P, l, im, v[im]);
+    if constexpr (factored<S>()) {
+      const R dp = round_store<S, R>(P, l, ip, R(0.5) * (sum + diff), rng, v[ip]);
+      const R dm = round_store<S, R>(P, l, im, R(0.5) * (sum - diff), rng, v[im]);
+      s0 += dp + dm;
+    } else {
+      v[ip] = to_store<S, R>(P, l, ip, R(0.5) * (sum + diff), rng);
+      v[im] = to_store<S, R>(P, l, im, R(0.5) * (sum - diff), rng);
+      s0 += from_store<S, R>(P, l, ip, v[ip]) + from_store<S, R>(P, l, im, v[im]);
+    }
+  }
+}
+
+// What the species collisions need of the flow: the velocity us the species see, T
+// and the diffusion velocities V_c, in the precision of the source F. Factored: the
+// values themselves. Else the triplets of Psi(us, R_c T) (pe) and of Psi(us) -
+// Psi(us + V_c) (pd).
+template <typename S, int M, bool FACTORED = factored<S>()>
+struct SpeciesFlow {
+  SrcF<S> u[3], zeta[M], V[M][3];
+  template <typename R, typename GetV>
+  __host__ __device__ __forceinline__ SpeciesFlow(const Params<R>& P, const R (&us)[3], R T, GetV&& getV)
+  {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) u[k] = SrcF<S>(us[k]);
+#pragma unroll
+    for (int c = 0; c < M; ++c) {
+      zeta[c] = SrcF<S>(T * P.inv_m[c]);
+#pragma unroll
+      for (int k = 0; k < 3; ++k) V[c][k] = SrcF<S>(getV(c, k));
+    }
+  }
+};
+
+template <typename S, int M>
+struct SpeciesFlow<S, M, false> {
+  Trip<SrcF<S>> pe[M][3], pd[M][3];
+  template <typename R, typename GetV>
+  __host__ __device__ __forceinline__ SpeciesFlow(const Params<R>& P, const R (&us)[3], R T, GetV&& getV)
+  {
+#pragma unroll
+    for (int c = 0; c < M; ++c) {
+      const SrcF<S> zeta = SrcF<S>(T * P.inv_m[c]);
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        pe[c][k] = psi_trip<SrcF<S>>(SrcF<S>(us[k]), zeta);
+        pd[c][k] = psi_diff_trip<SrcF<S>>(SrcF<S>(us[k]), SrcF<S>(getV(c, k)));
+      }
+    }
+  }
+};
+
+// F_i = sum_c K_c [Psi_i(u, R_c T) - Psi_i(u + V_c, R_c T)] of every direction: with e
+// the triplets of Psi(u) and d those of the difference, e e e - (e - d)(e - d)(e - d)
+// = d_x (e_y e_z) + (e - d)_x (d_y e_z + (e - d)_y d_z). The two (y, z) factors take
+// nine values each and K_c goes into the x factors: 81 operations per species c and
+// two per direction, where the direction-by-direction form takes about 160, and one
+// species' triplets at a time in registers.
+template <typename F, typename R, int M>
+__host__ __device__ __forceinline__ void species_source(const F (&u)[3], const F (&zeta)[M], const F (&V)[M][3],
+                                                        const R (&Ka)[M], F (&out)[Q])
+{
+#pragma unroll
+  for (int i = 0; i < Q; ++i) out[i] = F(0);
+#pragma unroll
+  for (int c = 0; c < M; ++c) {
+    Trip<F> e[3], d[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      e[k] = psi_trip<F>(u[k], zeta[c]);
+      d[k] = psi_diff_trip<F>(u[k], V[c][k]);
+    }
+    const F K = F(Ka[c]);
+    F kd[3], ke[3];
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+      kd[j] = K * d[0](j - 1);
+      ke[j] = K * (e[0](j - 1) - d[0](j - 1));
+    }
+#pragma unroll
+    for (int yz = 0; yz < 9; ++yz) {
+      const F ey = e[1](yz / 3 - 1), ez = e[2](yz % 3 - 1), dy = d[1](yz / 3 - 1), dz = d[2](yz % 3 - 1);
+      const F p = ey * ez, q = dy * ez + (ey - dy) * dz;
+#pragma unroll
+      for (int j = 0; j < 3; ++j) out[9 * j + yz] += kd[j] * p + ke[j] * q;
+    }
   }
 }
 
 // Species lattice a: f' = f + 2 beta (f^eq - f) + (beta - 1) F (eq SMlbm),
 // F_ai = sum_b K_ab [Psi_i(u, R_b T) - Psi_i(u + V_b, R_b T)] (eq fstar1), with
 // K_ab = P X_a X_b / D_ab, 1/tau_a = sum_b Y_b / tau_ab (eqs tauab, tau). us is
-// the velocity the species see, pe the triplets of Psi(us, R_c T) and pd those
-// of Psi(us) - Psi(us + V_c) (FP32 unless the storage is FP64: F is a small
-// correction); gD the factor (T_ref / T)^s_D of temperature-dependent transport
-// (1 otherwise).
+// the velocity the species see; F is evaluated in FP32 unless the storage is FP64
+// (a small correction); gD the factor (T_ref / T)^s_D of temperature-dependent
+// transport (1 otherwise).
 template <typename S, typename R, int M, int BC, bool CVT>
 __host__ __device__ __forceinline__ void species_relax(const Params<R>& P, const Mix<R, M>& s, const R (&K)[M][M],
-                                                       const Trip<SrcF<S>> (&pe)[M][3],
-                                                       const Trip<SrcF<S>> (&pd)[M][3], const R (&us)[3], R gD,
+                                                       const SpeciesFlow<S, M>& fl, const R (&us)[3], R gD,
                                                        int a, S (&v)[Q], S* __restrict__ dst, const Nbr& b,
                                                        int64_t node, uint32_t step)
 {
@@ -941,27 +1096,46 @@ __host__ __device__ __forceinline__ void species_relax(const Params<R>& P, const
 #pragma unroll
   for (int i = 0; i < Q; ++i) t0 += from_store<S, R>(P, a, i, v[i]);
   Rng rng(node, a, step);
+  if constexpr (factored<S>()) {
+    F32 F[Q];
+    species_source<F32, R, M>(fl.u, fl.zeta, fl.V, K[a], F);
+    const R b2 = R(2) * beta, b1 = R(1) - b2, bF = beta - R(1);
+    const R px[3] = {s.rho_a[a] * pa[0].m, s.rho_a[a] * pa[0].z, s.rho_a[a] * pa[0].p};
 #pragma unroll
-  for (int i = 0; i < Q; ++i) {
-    if (i == 13) continue;
-    F32 F = F32(0);
+    for (int xy = 0; xy < 9; ++xy) {
+      const R pxy = px[xy / 3] * pa[1](xy % 3 - 1);
 #pragma unroll
-    for (int c = 0; c < M; ++c) {
-      const F32 ex = pe[c][0](cx(i)), ey = pe[c][1](cy(i)), ez = pe[c][2](cz(i));
-      const F32 dx = pd[c][0](cx(i)), dy = pd[c][1](cy(i)), dz = pd[c][2](cz(i));
-      F += F32(K[a][c]) * (dx * ey * ez + (ex - dx) * dy * ez + (ex - dx) * (ey - dy) * dz);
+      for (int z = 0; z < 3; ++z) {
+        const int i = 3 * xy + z;
+        if (i == 13) continue;
+        const R fe = pxy * pa[2](z - 1) - P.ref[a][crep(i)];
+        // f' - f_ref = 2 beta (f^eq - f_ref) + (1 - 2 beta)(f - f_ref) + (beta - 1) F
+        const R dn = b2 * fe + (b1 * from_store<S, R>(P, a, i, v[i]) + bF * R(F[i]));
+        s0 += round_store<S, R>(P, a, i, dn, rng, v[i]);
+      }
     }
-    const R fe = s.rho_a[a] * (pa[0](cx(i)) * pa[1](cy(i)) * pa[2](cz(i))) - P.ref[a][crep(i)];
-    // f' - f_ref = (f^eq - f_ref) + (1 - 2 beta)(f - f^eq) + (beta - 1) F
-    const R dn = fe + (R(1) - R(2) * beta) * (from_store<S, R>(P, a, i, v[i]) - fe) + (beta - R(1)) * R(F);
-    v[i] = to_store<S, R>(P, a, i, dn, rng);
-    s0 += from_store<S, R>(P, a, i, v[i]);
+  } else {
+#pragma unroll
+    for (int i = 0; i < Q; ++i) {
+      if (i == 13) continue;
+      F32 F = F32(0);
+#pragma unroll
+      for (int c = 0; c < M; ++c) {
+        const F32 ex = fl.pe[c][0](cx(i)), ey = fl.pe[c][1](cy(i)), ez = fl.pe[c][2](cz(i));
+        const F32 dx = fl.pd[c][0](cx(i)), dy = fl.pd[c][1](cy(i)), dz = fl.pd[c][2](cz(i));
+        F += F32(K[a][c]) * (dx * ey * ez + (ex - dx) * dy * ez + (ex - dx) * (ey - dy) * dz);
+      }
+      const R fe = s.rho_a[a] * (pa[0](cx(i)) * pa[1](cy(i)) * pa[2](cz(i))) - P.ref[a][crep(i)];
+      // f' - f_ref = (f^eq - f_ref) + (1 - 2 beta)(f - f^eq) + (beta - 1) F
+      const R dn = fe + (R(1) - R(2) * beta) * (from_store<S, R>(P, a, i, v[i]) - fe) + (beta - R(1)) * R(F);
+      v[i] = to_store<S, R>(P, a, i, dn, rng);
+      s0 += from_store<S, R>(P, a, i, v[i]);
+    }
   }
   // the collision conserves rho_a: the rest population takes the defect of
   // the arithmetic and of the other 26 values' rounding to storage
   v[13] = to_store<S, R>(P, a, 13, t0 - s0, rng);
-#pragma unroll
-  for (int i = 0; i < Q; ++i) push<S, R, BC>(P, dst, b, a, i, node, v[i]);
+  push_all<S, R, BC>(P, dst, b, a, node, v);
   range_check<S, R>(P, rng);
 }
 
@@ -979,45 +1153,82 @@ __host__ __device__ __forceinline__ void momentum_relax(const Params<R>& P, int 
 #pragma unroll
   for (int k = 0; k < 3; ++k) pf[k] = psi_trip<R>(u[k], theta);
   R t0 = R(0), t1[3] = {R(0), R(0), R(0)}, s0 = R(0), s1[3] = {R(0), R(0), R(0)};
-  Rng rng(node, LF, step);
-#pragma unroll
-  for (int i = 0; i < Q; ++i) {
-    const R d = from_store<S, R>(P, LF, i, v[i]);
-    t0 += d;
-    acc_c(t1[0], cx(i), d);
-    acc_c(t1[1], cy(i), d);
-    acc_c(t1[2], cz(i), d);
-  }
-  // the source A_i . X adds X to the momentum (A_i = c_i / 2 on the six faces)
-#pragma unroll
-  for (int k = 0; k < 3; ++k) t1[k] += Xc[k];
-  // all but the rest and face populations: collide and round to storage
-#pragma unroll
-  for (int i = 0; i < Q; ++i) {
-    if (csq(i) <= 1) continue;
-    const R fe = rho * (pf[0](cx(i)) * pf[1](cy(i)) * pf[2](cz(i))) - P.ref[LF][crep(i)];
-    const R dn = fe + (R(1) - omega) * (from_store<S, R>(P, LF, i, v[i]) - fe);
-    v[i] = to_store<S, R>(P, LF, i, dn, rng);
-    const R d = from_store<S, R>(P, LF, i, v[i]);
-    s0 += d;
-    acc_c(s1[0], cx(i), d);
-    acc_c(s1[1], cy(i), d);
-    acc_c(s1[2], cz(i), d);
-  }
-  // the face pairs carry the momentum defect, the rest population the mass
-  // defect: each face pair keeps its equilibrium-relaxed sum and takes the
-  // difference that restores rho u + X exactly
   R face[Q];
+  Rng rng(node, LF, step);
+  if constexpr (factored<S>()) {
+    // opposite directions together: their sum carries the mass, their difference
+    // the momentum
+    t0 = from_store<S, R>(P, LF, 13, v[13]);
 #pragma unroll
-  for (int i = 0; i < Q; ++i) {
-    if (csq(i) != 1) continue;
-    const R fe = rho * (pf[0](cx(i)) * pf[1](cy(i)) * pf[2](cz(i))) - P.ref[LF][crep(i)];
-    face[i] = fe + (R(1) - omega) * (from_store<S, R>(P, LF, i, v[i]) - fe);
+    for (int i = 0; i < 13; ++i) {
+      const R dm = from_store<S, R>(P, LF, i, v[i]), dp = from_store<S, R>(P, LF, 26 - i, v[26 - i]);
+      t0 += dm + dp;
+      const R df = dm - dp;
+      acc_c(t1[0], cx(i), df);
+      acc_c(t1[1], cy(i), df);
+      acc_c(t1[2], cz(i), df);
+    }
+    // the source A_i . X adds X to the momentum (A_i = c_i / 2 on the six faces)
+#pragma unroll
+    for (int k = 0; k < 3; ++k) t1[k] += Xc[k];
+    const R px[3] = {rho * pf[0].m, rho * pf[0].z, rho * pf[0].p};
+    const R o1 = R(1) - omega;
+    auto relax = [&](int i) -> R {
+      const R fe = px[cx(i) + 1] * pf[1](cy(i)) * pf[2](cz(i)) - P.ref[LF][crep(i)];
+      return omega * fe + o1 * from_store<S, R>(P, LF, i, v[i]);
+    };
+    // all but the rest and face populations: collide and round to storage; the face
+    // pairs carry the momentum defect, the rest population the mass defect: each
+    // face pair keeps its equilibrium-relaxed sum and takes the difference that
+    // restores rho u + X exactly
+#pragma unroll
+    for (int i = 0; i < 13; ++i) {
+      if (csq(i) == 1) {
+        face[i] = relax(i);
+        face[26 - i] = relax(26 - i);
+        continue;
+      }
+      const R dm = round_store<S, R>(P, LF, i, relax(i), rng, v[i]);
+      const R dp = round_store<S, R>(P, LF, 26 - i, relax(26 - i), rng, v[26 - i]);
+      s0 += dm + dp;
+      const R df = dm - dp;
+      acc_c(s1[0], cx(i), df);
+      acc_c(s1[1], cy(i), df);
+      acc_c(s1[2], cz(i), df);
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < Q; ++i) {
+      const R d = from_store<S, R>(P, LF, i, v[i]);
+      t0 += d;
+      acc_c(t1[0], cx(i), d);
+      acc_c(t1[1], cy(i), d);
+      acc_c(t1[2], cz(i), d);
+    }
+#pragma unroll
+    for (int k = 0; k < 3; ++k) t1[k] += Xc[k];
+#pragma unroll
+    for (int i = 0; i < Q; ++i) {
+      if (csq(i) <= 1) continue;
+      const R fe = rho * (pf[0](cx(i)) * pf[1](cy(i)) * pf[2](cz(i))) - P.ref[LF][crep(i)];
+      const R dn = fe + (R(1) - omega) * (from_store<S, R>(P, LF, i, v[i]) - fe);
+      v[i] = to_store<S, R>(P, LF, i, dn, rng);
+      const R d = from_store<S, R>(P, LF, i, v[i]);
+      s0 += d;
+      acc_c(s1[0], cx(i), d);
+      acc_c(s1[1], cy(i), d);
+      acc_c(s1[2], cz(i), d);
+    }
+#pragma unroll
+    for (int i = 0; i < Q; ++i) {
+      if (csq(i) != 1) continue;
+      const R fe = rho * (pf[0](cx(i)) * pf[1](cy(i)) * pf[2](cz(i))) - P.ref[LF][crep(i)];
+      face[i] = fe + (R(1) - omega) * (from_store<S, R>(P, LF, i, v[i]) - fe);
+    }
   }
   restore_faces<S, R>(P, LF, face, t1, s1, s0, v, rng);
   v[13] = to_store<S, R>(P, LF, 13, t0 - s0, rng);
-#pragma unroll
-  for (int i = 0; i < Q; ++i) push<S, R, BC>(P, dst, b, LF, i, node, v[i]);
+  push_all<S, R, BC>(P, dst, b, LF, node, v);
   range_check<S, R>(P, rng);
 }
 
@@ -1049,26 +1260,62 @@ __host__ __device__ __forceinline__ void energy_relax(const Params<R>& P, int LG
   Rng rng(node, LG, step);
 #pragma unroll
   for (int i = 0; i < Q; ++i) t0 += from_store<S, R>(P, LG, i, v[i]);
+  if constexpr (factored<S>()) {
+    // opposite directions together: the equilibrium's even part, omega (w (rho E + ...)
+    // + B Z - f_ref), is one constant per direction class plus a term in (c . u)^2,
+    // the odd part of the equilibrium and the source share one vector; about 11
+    // operations per pair, where the direction-by-direction form takes about 45
+    const R o1 = R(1) - omega;
+    R bv[3];
 #pragma unroll
-  for (int i = 0; i < Q; ++i) {
-    if (i == 13) continue;
-    const R w = wt(cx(i)) * wt(cy(i)) * wt(cz(i));
-    const R cu = R(cx(i)) * u[0] + R(cy(i)) * u[1] + R(cz(i)) * u[2];
-    const R cqe = R(cx(i)) * qeq[0] + R(cy(i)) * qeq[1] + R(cz(i)) * qeq[2];
-    const R cdq = R(cx(i)) * dq[0] + R(cy(i)) * dq[1] + R(cz(i)) * dq[2];
-    R bz = R(0);
-    if (csq(i) == 1) bz = -R(0.5) * (cx(i) ? Z[0] : (cy(i) ? Z[1] : Z[2]));
-    const R ge = w * (rhoE + cqe * inv_theta +
-                      (rt2 * (R(csq(i)) - R(3) * theta) + kappa * (cu * cu - theta * usq)) * h2) + bz -
-                 P.ref[LG][crep(i)];
-    const R dn = ge + (R(1) - omega) * (from_store<S, R>(P, LG, i, v[i]) - ge) + w * cdq * inv_theta;
-    v[i] = to_store<S, R>(P, LG, i, dn, rng);
-    s0 += from_store<S, R>(P, LG, i, v[i]);
+    for (int k = 0; k < 3; ++k) bv[k] = (omega * qeq[k] + dq[k]) * inv_theta;
+    const R wk[4] = {wt.z * wt.z * wt.z, wt.p * wt.z * wt.z, wt.p * wt.p * wt.z, wt.p * wt.p * wt.p};
+    const R e0 = rhoE - kappa * theta * usq * h2;
+    const R okh = omega * kappa * h2;
+    R Ck[4], Wk[4];                                  // per |c|^2: omega w (...), omega w kappa / (2 theta^2)
+#pragma unroll
+    for (int k = 1; k < 4; ++k) {
+      Ck[k] = omega * wk[k] * (e0 + rt2 * h2 * (R(k) - R(3) * theta));
+      Wk[k] = wk[k] * okh;
+    }
+#pragma unroll
+    for (int i = 0; i < 13; ++i) {
+      const int k = csq(i), j = 26 - i;              // c_j = -c_i
+      R C = Ck[k] - omega * P.ref[LG][crep(i)];
+      if (k == 1) C -= omega * R(0.5) * (cx(i) ? Z[0] : (cy(i) ? Z[1] : Z[2]));
+      R cu = R(0), cb = R(0);
+      acc_c(cu, cx(i), u[0]);
+      acc_c(cu, cy(i), u[1]);
+      acc_c(cu, cz(i), u[2]);
+      acc_c(cb, cx(i), bv[0]);
+      acc_c(cb, cy(i), bv[1]);
+      acc_c(cb, cz(i), bv[2]);
+      const R A = C + Wk[k] * (cu * cu), B = wk[k] * cb;
+      const R dm = round_store<S, R>(P, LG, i, o1 * from_store<S, R>(P, LG, i, v[i]) + (A + B), rng, v[i]);
+      const R dp = round_store<S, R>(P, LG, j, o1 * from_store<S, R>(P, LG, j, v[j]) + (A - B), rng, v[j]);
+      s0 += dm + dp;
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < Q; ++i) {
+      if (i == 13) continue;
+      const R w = wt(cx(i)) * wt(cy(i)) * wt(cz(i));
+      const R cu = R(cx(i)) * u[0] + R(cy(i)) * u[1] + R(cz(i)) * u[2];
+      const R cqe = R(cx(i)) * qeq[0] + R(cy(i)) * qeq[1] + R(cz(i)) * qeq[2];
+      const R cdq = R(cx(i)) * dq[0] + R(cy(i)) * dq[1] + R(cz(i)) * dq[2];
+      R bz = R(0);
+      if (csq(i) == 1) bz = -R(0.5) * (cx(i) ? Z[0] : (cy(i) ? Z[1] : Z[2]));
+      const R ge = w * (rhoE + cqe * inv_theta +
+                        (rt2 * (R(csq(i)) - R(3) * theta) + kappa * (cu * cu - theta * usq)) * h2) + bz -
+                   P.ref[LG][crep(i)];
+      const R dn = ge + (R(1) - omega) * (from_store<S, R>(P, LG, i, v[i]) - ge) + w * cdq * inv_theta;
+      v[i] = to_store<S, R>(P, LG, i, dn, rng);
+      s0 += from_store<S, R>(P, LG, i, v[i]);
+    }
   }
   // the collision conserves rho E: the rest population takes the defect
   v[13] = to_store<S, R>(P, LG, 13, t0 - s0, rng);
-#pragma unroll
-  for (int i = 0; i < Q; ++i) push<S, R, BC>(P, dst, b, LG, i, node, v[i]);
+  push_all<S, R, BC>(P, dst, b, LG, node, v);
   range_check<S, R>(P, rng);
 }
 
@@ -1211,22 +1458,13 @@ __host__ __device__ __forceinline__ void collide_node(const Params<R>& P, const 
       gD = inv_diffusivity_factor<R>(P, s.T);
       Pk *= gD;
     }
-    friction_matrix<R, M>(P, s, Pk, present, K);
-      Trip<SrcF<S>> pe[M][3], pd[M][3];
-#pragma unroll
-    for (int c = 0; c < M; ++c) {
-      const SrcF<S> zeta = SrcF<S>(s.T * P.inv_m[c]);
-#pragma unroll
-      for (int k = 0; k < 3; ++k) {
-        pe[c][k] = psi_trip<SrcF<S>>(SrcF<S>(us[k]), zeta);
-        pd[c][k] = psi_diff_trip<SrcF<S>>(SrcF<S>(us[k]), SrcF<S>(get(RL::V + 3 * c + k)));
-      }
-    }
+    friction_matrix<R, M, sizeof(S) >= 4>(P, s, Pk, present, K);
+    const SpeciesFlow<S, M> fl(P, us, s.T, [&](int c, int k) -> R { return get(RL::V + 3 * c + k); });
 #pragma unroll
     for (int a = 0; a < NS; ++a) {
       S v[Q];
       load(a, v);
-      species_relax<S, R, M, BC, CVT>(P, s, K, pe, pd, us, gD, a, v, dst, b, node, step);
+      species_relax<S, R, M, BC, CVT>(P, s, K, fl, us, gD, a, v, dst, b, node, step);
       lattice_barrier();
     }
   }
@@ -1302,28 +1540,56 @@ enum {
   REC2_FIELDS = 10
 };
 
-template <typename S, typename R, typename Rec, int M, int BC, bool WEAK = false>
+// Where state_species_node keeps the species populations between the moments and the
+// collision. One stored species, and three or more in FP64 arithmetic (whose kernel
+// has the whole register file at one wave per SIMD): registers, every load of the
+// node issued at the start. Two with 4-byte storage: LDS, 55 KB per workgroup, two
+// workgroups per compute unit. The rest read them a second time: eight waves' values
+// of all lattices do not stay in an XCD's 4 MB of L2, so the second read costs
+// nearly a first one (512 ternary tubes: 3.05 ms, read twice 3.39 ms; weak coupling,
+// 1.5 M nodes: 212 us, read twice 234 us; jets 200 x 400, M = 4: 36 us against 41 us).
+enum { HOLD_REG, HOLD_LDS, HOLD_NONE };
+template <typename S, typename R, int M, bool WEAK>
+constexpr int hold_mode()
+{
+  constexpr int NS = Lat<M, WEAK>::NS;
+  if (NS == 1) return HOLD_REG;
+  if (sizeof(S) != 4) return HOLD_NONE;
+  if (NS == 2) return HOLD_LDS;
+  return sizeof(R) == 8 ? HOLD_REG : HOLD_NONE;
+}
+
+// held: this thread's column of the LDS array (HOLD_LDS), values HS apart.
+template <typename S, typename R, typename Rec, int M, int BC, bool WEAK, int HS>
 __host__ __device__ __forceinline__ void state_species_node(const Params<R>& P, const S* __restrict__ src,
                                                             S* __restrict__ dst, Rec* __restrict__ rec,
-                                                            int64_t node, uint32_t step)
+                                                            int64_t node, uint32_t step, S* held)
 {
   const size_t n = (size_t)P.n;
   const uint32_t nd = (uint32_t)node;
   constexpr int NS = Lat<M, WEAK>::NS, LF = Lat<M, WEAK>::LF, LG = Lat<M, WEAK>::LG;
-  // species lattices: kept in registers for their collision below when there is
-  // one (binary, strong coupling); with more, the state's registers are needed
-  // for the larger Stefan--Maxwell system, and the values are read again for the
-  // collision (the first read is a cached load, so the second mostly hits L2)
-  constexpr bool HOLD = NS == 1;
-  S vs[HOLD ? NS : 1][Q];
+  constexpr int HOLD = hold_mode<S, R, M, WEAK>();
+  S vs[HOLD == HOLD_REG ? NS : 1][Q];
+  if constexpr (HOLD == HOLD_REG && NS > 1) {
+#pragma unroll
+    for (int a = 0; a < NS; ++a)
+#pragma unroll
+      for (int i = 0; i < Q; ++i) vs[a][i] = buf_load<S, BUF_NT>(src + (size_t)(a * Q + i) * n, (uint32_t)n, nd);
+    lattice_barrier();
+  }
   R rho_s[M], js[M][3];
 #pragma unroll
   for (int a = 0; a < NS; ++a) {
-    S (&va)[Q] = vs[HOLD ? a : 0];
-    if constexpr (HOLD) load_lattice(src + (size_t)a * Q * n, n, nd, va);
-    else
+    S (&va)[Q] = vs[HOLD == HOLD_REG ? a : 0];
+    if constexpr (HOLD == HOLD_LDS || NS == 1) load_lattice(src + (size_t)a * Q * n, n, nd, va);
+    if constexpr (HOLD == HOLD_NONE) {
 #pragma unroll
       for (int i = 0; i < Q; ++i) va[i] = buf_load<S>(src + (size_t)(a * Q + i) * n, (uint32_t)n, nd);
+    }
+    if constexpr (HOLD == HOLD_LDS) {
+#pragma unroll
+      for (int i = 0; i < Q; ++i) held[(a * Q + i) * HS] = va[i];
+    }
     R r = R(0), ja[3] = {R(0), R(0), R(0)};
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
@@ -1338,16 +1604,41 @@ __host__ __device__ __forceinline__ void state_species_node(const Params<R>& P, 
     for (int k = 0; k < 3; ++k) js[a][k] = ja[k];
   }
   if constexpr (!WEAK) rho_s[M - 1] = R(0);
-  // mixture moments: rho, rho u (momentum lattice) and rho E (energy lattice)
+  // mixture moments: rho, rho u (momentum lattice) and rho E (energy lattice). With
+  // FP64 and FP32 storage the loads of a lattice, and with two species of both, are
+  // issued together (left to itself the scheduler keeps one load in flight here:
+  // weak coupling, 1.5 M nodes, 424 -> 234 us)
   R rho = R(0), j[3] = {R(0), R(0), R(0)}, rhoE = R(0);
+  if constexpr (factored<S>()) {
+    S vf[Q], vg[Q];
 #pragma unroll
-  for (int i = 0; i < Q; ++i) {
-    const R d = from_store<S, R>(P, LF, i, buf_load<S, BUF_NT>(src + (size_t)(LF * Q + i) * n, (uint32_t)n, nd));
-    rho += d;
-    acc_c(j[0], cx(i), d);
-    acc_c(j[1], cy(i), d);
-    acc_c(j[2], cz(i), d);
-    rhoE += from_store<S, R>(P, LG, i, buf_load<S, BUF_NT>(src + (size_t)(LG * Q + i) * n, (uint32_t)n, nd));
+    for (int i = 0; i < Q; ++i) vf[i] = buf_load<S, BUF_NT>(src + (size_t)(LF * Q + i) * n, (uint32_t)n, nd);
+    if constexpr (M == 2) load_lattice(src + (size_t)LG * Q * n, n, nd, vg);
+    else lattice_barrier();
+    rho = R(vf[13]);
+#pragma unroll
+    for (int i = 0; i < 13; ++i) {
+      const R dm = R(vf[i]), dp = R(vf[26 - i]);
+      rho += dm + dp;
+      const R df = dm - dp;
+      acc_c(j[0], cx(i), df);
+      acc_c(j[1], cy(i), df);
+      acc_c(j[2], cz(i), df);
+    }
+    if constexpr (M != 2) load_lattice(src + (size_t)LG * Q * n, n, nd, vg);
+    rhoE = R(vg[13]);
+#pragma unroll
+    for (int i = 0; i < 13; ++i) rhoE += R(vg[i]) + R(vg[26 - i]);
+  } else {
+#pragma unroll
+    for (int i = 0; i < Q; ++i) {
+      const R d = from_store<S, R>(P, LF, i, buf_load<S, BUF_NT>(src + (size_t)(LF * Q + i) * n, (uint32_t)n, nd));
+      rho += d;
+      acc_c(j[0], cx(i), d);
+      acc_c(j[1], cy(i), d);
+      acc_c(j[2], cz(i), d);
+      rhoE += from_store<S, R>(P, LG, i, buf_load<S, BUF_NT>(src + (size_t)(LG * Q + i) * n, (uint32_t)n, nd));
+    }
   }
   rho += P.ref0[LF];
   rhoE += P.ref0[LG];
@@ -1379,7 +1670,7 @@ __host__ __device__ __forceinline__ void state_species_node(const Params<R>& P, 
   bool present[M];
   species_present<R, M>(P, s.rho_a, s.rho, present);
   R K[M][M], V[M][3];
-  friction_matrix<R, M>(P, s, Pk, present, K);
+  friction_matrix<R, M, sizeof(S) >= 4>(P, s, Pk, present, K);
   diffusion_velocities<R, M>(s, present, K, js, us, V);
   const R theta = s.Rg * s.T;
   const R mu_mix = mixture_viscosity<R, M>(P, s.X);
@@ -1401,22 +1692,17 @@ __host__ __device__ __forceinline__ void state_species_node(const Params<R>& P, 
     put(REC2_HYV + k, h);
   }
   // species collisions and streaming
-  Trip<SrcF<S>> pe[M][3], pd[M][3];
-#pragma unroll
-  for (int c = 0; c < M; ++c) {
-    const SrcF<S> zeta = SrcF<S>(s.T * P.inv_m[c]);
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      pe[c][k] = psi_trip<SrcF<S>>(SrcF<S>(us[k]), zeta);
-      pd[c][k] = psi_diff_trip<SrcF<S>>(SrcF<S>(us[k]), SrcF<S>(V[c][k]));
-    }
-  }
+  const SpeciesFlow<S, M> fl(P, us, s.T, [&](int c, int k) -> R { return V[c][k]; });
   const Nbr b = neighbours(P, node);
 #pragma unroll
   for (int a = 0; a < NS; ++a) {
-    S (&va)[Q] = vs[HOLD ? a : 0];
-    if constexpr (!HOLD) load_lattice(src + (size_t)a * Q * n, n, nd, va);
-    species_relax<S, R, M, BC, false>(P, s, K, pe, pd, us, R(1), a, va, dst, b, node, step);
+    S (&va)[Q] = vs[HOLD == HOLD_REG ? a : 0];
+    if constexpr (HOLD == HOLD_NONE) load_lattice(src + (size_t)a * Q * n, n, nd, va);
+    if constexpr (HOLD == HOLD_LDS) {
+#pragma unroll
+      for (int i = 0; i < Q; ++i) va[i] = held[(a * Q + i) * HS];
+    }
+    species_relax<S, R, M, BC, false>(P, s, K, fl, us, R(1), a, va, dst, b, node, step);
     lattice_barrier();
   }
 }
@@ -1430,36 +1716,97 @@ __host__ __device__ __forceinline__ void fg_collide_node(const Params<R>& P, con
   const uint32_t nd = (uint32_t)node;
   constexpr int LF = Lat<M, WEAK>::LF, LG = Lat<M, WEAK>::LG;
   S vf[Q], vg[Q];
-  load_lattice(src + (size_t)LF * Q * n, n, nd, vf);
-  load_lattice(src + (size_t)LG * Q * n, n, nd, vg);
+  auto get = [&](int f) -> R { return R(*at32(rec + (size_t)f * n, nd)); };
+  // FP32 storage without reflecting walls: every load of the node (both lattices, the
+  // record, the stencil) is issued before the first is used; the kernel waits for
+  // memory with two waves per SIMD, and loads after the moments cost it a second
+  // latency (shear layer 256^3: 1.76 -> 1.63 ms). The walls' store offsets leave no
+  // registers for it (512 ternary tubes: 2.64 ms so, 2.19 ms with the stencil loaded
+  // after the moments), nor does FP64 storage (64 x 8 x 8: 9.7 -> 12.3 us); the
+  // 16-bit kernels are bound by instructions (190 x 164 x 156 fixed point: 466 -> 500
+  // us).
+  constexpr bool EARLY = sizeof(S) == 4 && !reflecting(BC);
+  const Nbr b = neighbours(P, node);
+  if constexpr (EARLY) {
+#pragma unroll
+    for (int i = 0; i < Q; ++i) vf[i] = buf_load<S, BUF_NT>(src + (size_t)(LF * Q + i) * n, (uint32_t)n, nd);
+  } else {
+    load_lattice(src + (size_t)LF * Q * n, n, nd, vf);
+    load_lattice(src + (size_t)LG * Q * n, n, nd, vg);
+  }
+  // the record, and the stencil: 26 neighbours' C_p and, of each G_k, the 18 with c_k != 0
+  R omega, omega1, Cp, Rg, hyv[3];
+  Rec cpn[EARLY ? Q : 1], gn[3][EARLY ? Q : 1];
+  if constexpr (EARLY) {
+#pragma unroll
+    for (int i = 0; i < Q; ++i) vg[i] = buf_load<S, BUF_NT>(src + (size_t)(LG * Q + i) * n, (uint32_t)n, nd);
+    omega = get(REC_OMEGA), omega1 = get(REC2_OMEGA1), Cp = get(REC_CP), Rg = get(REC2_RG);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) hyv[k] = get(REC2_HYV + k);
+#pragma unroll
+    for (int i = 0; i < Q; ++i) {
+      if (csq(i) == 0) continue;
+      const uint32_t nb = stencil_index<BC>(b, cx(i), cy(i), cz(i));
+      cpn[i] = *at32(rec + (size_t)REC_CP * n, nb);
+      if (cx(i)) gn[0][i] = *at32(G, nb);
+      if (cy(i)) gn[1][i] = *at32(G + n, nb);
+      if (cz(i)) gn[2][i] = *at32(G + 2 * n, nb);
+    }
+    lattice_barrier();
+  }
   // moments: rho, rho u, the pressure tensor sum_i f_i c_i c_i, rho E and q
   R rho = R(0), j[3] = {R(0), R(0), R(0)}, Pd[3] = {R(0), R(0), R(0)}, Pxy = R(0), Pxz = R(0), Pyz = R(0);
   R rhoE = R(0), q[3] = {R(0), R(0), R(0)};
+  if constexpr (factored<S>()) {
+    rho = R(vf[13]);
+    rhoE = R(vg[13]);
 #pragma unroll
-  for (int i = 0; i < Q; ++i) {
-    const R d = from_store<S, R>(P, LF, i, vf[i]);
-    rho += d;
-    acc_c(j[0], cx(i), d);
-    acc_c(j[1], cy(i), d);
-    acc_c(j[2], cz(i), d);
-    if (cx(i)) Pd[0] += d;
-    if (cy(i)) Pd[1] += d;
-    if (cz(i)) Pd[2] += d;
-    acc_c(Pxy, cx(i) * cy(i), d);
-    acc_c(Pxz, cx(i) * cz(i), d);
-    acc_c(Pyz, cy(i) * cz(i), d);
-    const R e = from_store<S, R>(P, LG, i, vg[i]);
-    rhoE += e;
-    acc_c(q[0], cx(i), e);
-    acc_c(q[1], cy(i), e);
-    acc_c(q[2], cz(i), e);
+    for (int i = 0; i < 13; ++i) {
+      const R dm = R(vf[i]), dp = R(vf[26 - i]);
+      const R ds = dm + dp, df = dm - dp;
+      rho += ds;
+      acc_c(j[0], cx(i), df);
+      acc_c(j[1], cy(i), df);
+      acc_c(j[2], cz(i), df);
+      if (cx(i)) Pd[0] += ds;
+      if (cy(i)) Pd[1] += ds;
+      if (cz(i)) Pd[2] += ds;
+      acc_c(Pxy, cx(i) * cy(i), ds);
+      acc_c(Pxz, cx(i) * cz(i), ds);
+      acc_c(Pyz, cy(i) * cz(i), ds);
+      const R em = R(vg[i]), ep = R(vg[26 - i]);
+      rhoE += em + ep;
+      const R ef = em - ep;
+      acc_c(q[0], cx(i), ef);
+      acc_c(q[1], cy(i), ef);
+      acc_c(q[2], cz(i), ef);
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < Q; ++i) {
+      const R d = from_store<S, R>(P, LF, i, vf[i]);
+      rho += d;
+      acc_c(j[0], cx(i), d);
+      acc_c(j[1], cy(i), d);
+      acc_c(j[2], cz(i), d);
+      if (cx(i)) Pd[0] += d;
+      if (cy(i)) Pd[1] += d;
+      if (cz(i)) Pd[2] += d;
+      acc_c(Pxy, cx(i) * cy(i), d);
+      acc_c(Pxz, cx(i) * cz(i), d);
+      acc_c(Pyz, cy(i) * cz(i), d);
+      const R e = from_store<S, R>(P, LG, i, vg[i]);
+      rhoE += e;
+      acc_c(q[0], cx(i), e);
+      acc_c(q[1], cy(i), e);
+      acc_c(q[2], cz(i), e);
+    }
   }
   rho += P.ref0[LF];
   rhoE += P.ref0[LG];
 #pragma unroll
   for (int k = 0; k < 3; ++k) Pd[k] += P.ref2[LF][k];
-  auto get = [&](int f) -> R { return R(*at32(rec + (size_t)f * n, nd)); };
-  const R omega = get(REC_OMEGA), omega1 = get(REC2_OMEGA1), Cp = get(REC_CP), Rg = get(REC2_RG);
+  if constexpr (!EARLY) omega = get(REC_OMEGA), omega1 = get(REC2_OMEGA1), Cp = get(REC_CP), Rg = get(REC2_RG);
   const R inv_rho = R(1) / rho;
   R u[3], usq = R(0);
 #pragma unroll
@@ -1471,20 +1818,29 @@ __host__ __device__ __forceinline__ void fg_collide_node(const Params<R>& P, con
   const R theta = Rg * T;
   const R Pp = rho * Rg * T;
   // non-local terms: X_a = -d_a G_a (eq Xalpha) and d C_p (sum_a H_a d Y_a = T d C_p)
-  const Nbr b = neighbours(P, node);
   R dG[3] = {R(0), R(0), R(0)}, gcp[3] = {R(0), R(0), R(0)};
 #pragma unroll
   for (int i = 0; i < Q; ++i) {
     if (csq(i) == 0) continue;
-    const uint32_t nb = stencil_index<BC>(b, cx(i), cy(i), cz(i));
     const R w3 = R(3.0 * w13(i));
-    const R cpn = w3 * R(*at32(rec + (size_t)REC_CP * n, nb));
-    acc_c(gcp[0], cx(i), cpn);
-    acc_c(gcp[1], cy(i), cpn);
-    acc_c(gcp[2], cz(i), cpn);
-    if (cx(i)) acc_c(dG[0], cx(i), w3 * R(*at32(G, nb)));
-    if (cy(i)) acc_c(dG[1], cy(i), w3 * R(*at32(G + n, nb)));
-    if (cz(i)) acc_c(dG[2], cz(i), w3 * R(*at32(G + 2 * n, nb)));
+    if constexpr (EARLY) {
+      const R cpw = w3 * R(cpn[i]);
+      acc_c(gcp[0], cx(i), cpw);
+      acc_c(gcp[1], cy(i), cpw);
+      acc_c(gcp[2], cz(i), cpw);
+      if (cx(i)) acc_c(dG[0], cx(i), w3 * R(gn[0][i]));
+      if (cy(i)) acc_c(dG[1], cy(i), w3 * R(gn[1][i]));
+      if (cz(i)) acc_c(dG[2], cz(i), w3 * R(gn[2][i]));
+    } else {
+      const uint32_t nb = stencil_index<BC>(b, cx(i), cy(i), cz(i));
+      const R cpw = w3 * R(*at32(rec + (size_t)REC_CP * n, nb));
+      acc_c(gcp[0], cx(i), cpw);
+      acc_c(gcp[1], cy(i), cpw);
+      acc_c(gcp[2], cz(i), cpw);
+      if (cx(i)) acc_c(dG[0], cx(i), w3 * R(*at32(G, nb)));
+      if (cy(i)) acc_c(dG[1], cy(i), w3 * R(*at32(G + n, nb)));
+      if (cz(i)) acc_c(dG[2], cz(i), w3 * R(*at32(G + 2 * n, nb)));
+    }
   }
   const R Xc[3] = {-dG[0], -dG[1], -dG[2]};
   // energy source: the non-equilibrium flux q - q^eq - u.(P - P^eq) of this node
@@ -1498,7 +1854,7 @@ __host__ __device__ __forceinline__ void fg_collide_node(const Params<R>& P, con
 #pragma unroll
     for (int c = 0; c < 3; ++c) up += u[c] * (Pn[c][k] - (c == k ? Pp : R(0)) - rho * u[c] * u[k]);
     const R qn = q[k] - hyd * rho * u[k] - up;
-    dq[k] = (omega - omega1) * qn + omega1 * rho * T * get(REC2_HYV + k) + R(0.5) * (R(2) - omega1) * Pp * T * gcp[k];
+    dq[k] = (omega - omega1) * qn + omega1 * rho * T * (EARLY ? hyv[k] : get(REC2_HYV + k)) + R(0.5) * (R(2) - omega1) * Pp * T * gcp[k];
   }
   momentum_relax<S, R, BC>(P, LF, rho, u, theta, omega, Xc, vf, dst, b, node, step);
   lattice_barrier();
