@@ -113,83 +113,108 @@ __device__ inline int64_t wrap_index(const NTube& tb, int x, int y, int z)
 // Node p of the tile reads row p + 1 + dx while x + dx stays in the tube (the node
 // p + dx of the same x row); beyond a wall the forward reads row p + 1 (replicate
 // padding) and the adjoint zero, plus row p + 1 as the ghost's share at a wall
-// node. The next group's rows are loaded into registers while the
-// current group's products run.
-template <int CIN, int COUT, int EPI>
-__global__ __launch_bounds__(256) void k_conv(const NTube* __restrict__ tubes, const int32_t* __restrict__ tile_tube,
-                                                int ntubes, const bf16* __restrict__ W, const float* __restrict__ bias,
-                                                const bf16* __restrict__ in, const bf16* __restrict__ mask,
-                                                void* __restrict__ out)
+// node. The next group's rows and its three taps' weights are loaded into registers
+// while the current group's products run, and stored to LDS between two barriers.
+// The loads stand under no branch, and a step's operands are read from LDS two steps
+// ahead of its MFMAs: with a load under a branch the wave waits for it where the
+// branch ends, and the kernel spent as long in those waits as in its products (the
+// 64 -> 64 forward on 1.05 M nodes: 229 -> 200 us, 1.16 PFLOP/s, the rate a large library
+// product reaches; halving the barriers alone: 236 us). Two workgroups fit in a compute
+// unit: 64.8 KB of LDS each, rows padded by 16 bytes so that the 16 rows a quarter of a
+// wavefront reads at one piece cover the 64 banks once.
+//
+// FLAT (every tube one node wide in y and z): the nodes of all tubes form one row,
+// tile t takes its nodes 256 t .. 256 t + 255 whatever tubes they belong to, and `ends`
+// tells the first (bit 0) and last (bit 1) node of each tube. A tile of its own per
+// tube leaves 44% of the tiles' nodes idle on 4096 tubes of 32..256 nodes. The nine
+// groups take the same rows, so a wave keeps its operands of the three taps in
+// registers and reads only weights (half the LDS traffic, and the adjoint's wall
+// terms once instead of nine times: 64 -> 64 adjoint 129 -> 104 us).
+// Together, the eleven conv launches of a training iteration: 1.95 -> 0.96 ms.
+// Every node's products and their order are the same as without FLAT.
+template <int CIN>
+__device__ __forceinline__ int lds_at(int row, int c) { return row * (CIN + 8) + (c << 3); }
+
+template <int CIN, int COUT, int EPI, bool FLAT>
+constexpr int conv_waves()
 {
+  return COUT == 64 && (CIN == 64 || (EPI == 2 && !FLAT)) ? 2 : 3;   // what fits without spilling
+}
+
+template <int CIN, int COUT, int EPI, bool FLAT>
+__global__ __launch_bounds__(256, (conv_waves<CIN, COUT, EPI, FLAT>())) void k_conv(const NTube* __restrict__ tubes, const int32_t* __restrict__ tile_tube,
+                                                 int ntubes, const uint8_t* __restrict__ ends,
+                                                 const bf16* __restrict__ W, const float* __restrict__ bias,
+                                                 const bf16* __restrict__ in, const bf16* __restrict__ mask,
+                                                 void* __restrict__ out)
+{
+  constexpr int LS = CIN + 8;              // LDS row stride (bf16)
   static_assert(CIN % 16 == 0 && COUT % 32 == 0, "channel counts must fit the 32x32x16 MFMA");
   constexpr int SIGN = EPI == 2 ? -1 : 1;
-  constexpr int LS = CIN + 8;              // LDS row stride (bf16) of weights and staged rows
   constexpr int MB = COUT / 32;
   constexpr int KC = CIN / 16;
   constexpr int CHUNKS = COUT * CIN / 8;   // 16-byte pieces of one tap's weights
   constexpr int PT = (CHUNKS + 255) / 256;
   constexpr int RCH = CIN / 8;             // 16-byte pieces of one staged row
   static_assert(2 * RCH <= 256, "the two extra rows are spread over the first threads");
-  __shared__ __attribute__((aligned(16))) bf16 wl[2][COUT * LS];
+  __shared__ __attribute__((aligned(16))) bf16 wl[3][COUT * LS];
   __shared__ __attribute__((aligned(16))) bf16 sl[(TILE + 2) * LS];
 
   const int tile = xcd_tile((int)blockIdx.x, (int)gridDim.x);
-  const NTube tb = tube_of(tubes, tile_tube, ntubes, tile);
+  NTube tb = FLAT ? tubes[0] : tube_of(tubes, tile_tube, ntubes, tile);
+  if (FLAT) tb.base = 0;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int n_t = tb.nx * tb.ny * tb.nz;
-  const int t0 = (tile - tb.first_tile) * TILE;
-  int pos[2], xs[2];
-  bool valid[2];
+  const int n_t = FLAT ? (int)tb.ntot : tb.nx * tb.ny * tb.nz;
+  const int t0 = FLAT ? tile * TILE : (tile - tb.first_tile) * TILE;
+  int pos[2];
+  bool valid[2], lo[2], hi[2];             // in the tube(s); first, last node of an x row
 #pragma unroll
   for (int b = 0; b < 2; ++b) {
     pos[b] = wave * 64 + b * 32 + (lane & 31);
     valid[b] = t0 + pos[b] < n_t;
-    xs[b] = valid[b] ? (t0 + pos[b]) % tb.nx : 0;
+    if (FLAT) {
+      const int e = valid[b] ? ends[t0 + pos[b]] : 0;
+      lo[b] = e & 1;
+      hi[b] = e & 2;
+    } else {
+      const int x = valid[b] ? (t0 + pos[b]) % tb.nx : 0;
+      lo[b] = x == 0;
+      hi[b] = x == tb.nx - 1;
+    }
   }
   // staged rows of this thread: row threadIdx.x (all its pieces), and one piece
   // of the rows TILE and TILE + 1 on the first 2 RCH threads
-  const int r1 = TILE + (int)threadIdx.x / RCH, c1 = (int)threadIdx.x % RCH;
+  // (the other threads load their own row's first piece again). A row outside the
+  // tube is the nearest one inside: no node of the tube uses it, and loads under a
+  // branch would be waited for at its end, before the products they are to overlap.
   const bool extra = threadIdx.x < 2 * RCH;
+  const int r1 = TILE + (int)threadIdx.x / RCH, c1 = extra ? (int)threadIdx.x % RCH : 0;
   int jx[2], jy[2], jz[2];
-  bool jin[2];
   {
-    const int rows[2] = {(int)threadIdx.x, r1};
+    const int rows[2] = {(int)threadIdx.x, extra ? r1 : (int)threadIdx.x};
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
       const int j = t0 + rows[k] - 1;
-      jin[k] = j >= 0 && j < n_t && (k == 0 || extra);
-      const int i = jin[k] ? j : 0;
-      jx[k] = i % tb.nx;
-      const int r = i / tb.nx;
-      jy[k] = r % tb.ny;
-      jz[k] = r / tb.ny;
+      const int i = j < 0 ? 0 : (j < n_t ? j : n_t - 1);
+      jx[k] = FLAT ? i : i % tb.nx;
+      const int r = FLAT ? 0 : i / tb.nx;
+      jy[k] = FLAT ? 0 : r % tb.ny;
+      jz[k] = FLAT ? 0 : r / tb.ny;
     }
   }
   bf16x8 sreg[RCH], sx1;
   auto sload = [&](int g) {
     const int dy = SIGN * (g % 3 - 1), dz = SIGN * (g / 3 - 1);
-    const int64_t nb0 = wrap_index(tb, jx[0], jy[0] + dy, jz[0] + dz);
+    const int64_t nb0 = FLAT ? jx[0] : wrap_index(tb, jx[0], jy[0] + dy, jz[0] + dz);
+    const int64_t nb1 = FLAT ? jx[1] : wrap_index(tb, jx[1], jy[1] + dy, jz[1] + dz);
 #pragma unroll
-    for (int c = 0; c < RCH; ++c) {
-      if (jin[0]) {
-        sreg[c] = *(const bf16x8*)(in + aidx(tb, nb0, c * 8));
-      } else {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) sreg[c][e] = (bf16)0.f;
-      }
-    }
-    if (jin[1]) {
-      const int64_t nb1 = wrap_index(tb, jx[1], jy[1] + dy, jz[1] + dz);
-      sx1 = *(const bf16x8*)(in + aidx(tb, nb1, c1 * 8));
-    } else {
-#pragma unroll
-      for (int e = 0; e < 8; ++e) sx1[e] = (bf16)0.f;
-    }
+    for (int c = 0; c < RCH; ++c) sreg[c] = *(const bf16x8*)(in + aidx(tb, nb0, c * 8));
+    sx1 = *(const bf16x8*)(in + aidx(tb, nb1, c1 * 8));
   };
   auto sstore = [&]() {
 #pragma unroll
-    for (int c = 0; c < RCH; ++c) *(bf16x8*)(&sl[threadIdx.x * LS + c * 8]) = sreg[c];
-    if (extra) *(bf16x8*)(&sl[r1 * LS + c1 * 8]) = sx1;
+    for (int c = 0; c < RCH; ++c) *(bf16x8*)(&sl[lds_at<CIN>((int)threadIdx.x, c)]) = sreg[c];
+    if (extra) *(bf16x8*)(&sl[lds_at<CIN>(r1, c1)]) = sx1;
   };
   f32x16 acc[MB][2];
 #pragma unroll
@@ -199,90 +224,107 @@ __global__ __launch_bounds__(256) void k_conv(const NTube* __restrict__ tubes, c
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[mb][b][v] = 0.f;
 
-  bf16x8 wreg[PT];
-  auto load_w = [&](int tap) {
+  bf16x8 wreg[3][PT];
+  auto load_w = [&](int tap, int slot) {
 #pragma unroll
     for (int p = 0; p < PT; ++p) {
       const int ch = threadIdx.x + p * 256;
-      if (ch < CHUNKS) wreg[p] = *(const bf16x8*)(W + (size_t)tap * COUT * CIN + (size_t)ch * 8);
+      if (CHUNKS % 256 == 0 || ch < CHUNKS) wreg[slot][p] = *(const bf16x8*)(W + (size_t)tap * COUT * CIN + (size_t)ch * 8);
     }
   };
-  auto store_w = [&](int buf) {
+  auto store_w = [&](int slot) {
 #pragma unroll
     for (int p = 0; p < PT; ++p) {
       const int ch = threadIdx.x + p * 256;
-      if (ch < CHUNKS) {
-        const int row = ch / (CIN / 8), col = (ch % (CIN / 8)) * 8;
-        *(bf16x8*)(&wl[buf][row * LS + col]) = wreg[p];
-      }
+      if (CHUNKS % 256 == 0 || ch < CHUNKS) *(bf16x8*)(&wl[slot][lds_at<CIN>(ch / RCH, ch % RCH)]) = wreg[slot][p];
     }
   };
-  const int khalf = 8 * (lane >> 5);
-  // a tube one node wide in y and z wraps every (dy, dz) onto the node itself:
-  // the nine groups stage the same rows, so they are staged once
-  const bool restage = tb.ny > 1 || tb.nz > 1;
-  sload(0);
-  sstore();
-  load_w(0);
-  store_w(0);
-  __syncthreads();
-  for (int g = 0; g < 9; ++g) {
-    if (g + 1 < 9 && restage) sload(g + 1);
+  const int khalf = lane >> 5;             // which of an MFMA step's two 8-channel pieces
+  // one 16-channel step of a group's three taps: step s is tap dx index s / KC
+  constexpr int STEPS = 3 * KC;
+  auto rows_at = [&](int s, bf16x8 (&v)[2]) {
+    const int dx = SIGN * (s / KC - 1), c = 2 * (s % KC) + khalf;
 #pragma unroll
-    for (int d = 0; d < 3; ++d) {
-      const int tap = 3 * g + d;
-      const int buf = tap & 1;
-      if (tap + 1 < NTAP) load_w(tap + 1);
-      const int dx = SIGN * (d - 1);
-      bf16x8 bop[2][KC];
+    for (int b = 0; b < 2; ++b) {
+      const bool inside = dx < 0 ? !lo[b] : (dx > 0 ? !hi[b] : true);
+      v[b] = *(const bf16x8*)(&sl[lds_at<CIN>(pos[b] + 1 + (inside ? dx : 0), c)]);
+    }
+  };
+  auto at_walls = [&](int s, bf16x8 (&v)[2]) {
+    if constexpr (SIGN < 0) {
+      const int dx = SIGN * (s / KC - 1), c = 2 * (s % KC) + khalf;
 #pragma unroll
       for (int b = 0; b < 2; ++b) {
-        const int x = xs[b] + dx;
-        const bool inside = x >= 0 && x < tb.nx;
-        const int row = pos[b] + 1 + (inside ? dx : 0);
-        const bool use = valid[b] && (SIGN > 0 || inside);
+        if ((dx < 0 && lo[b]) || (dx > 0 && hi[b])) {
 #pragma unroll
-        for (int kc = 0; kc < KC; ++kc) {
-          if (use) {
-            bop[b][kc] = *(const bf16x8*)(&sl[row * LS + kc * 16 + khalf]);
-          } else {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) bop[b][kc][e] = (bf16)0.f;
-          }
+          for (int e = 0; e < 8; ++e) v[b][e] = (bf16)0.f;
         }
-        if constexpr (SIGN < 0) {
-          // the ghost's share: at a wall node the forward took the ghost of tap
-          // dx = -1 at x = 0 (dx = +1 at x = nx - 1) from the wall node itself, so
-          // the wall node also collects in(wall node) under that tap; the two
-          // operands are added in FP32 and rounded once
-          const bool wall = valid[b] && ((xs[b] == 0 && dx == 1) || (xs[b] == tb.nx - 1 && dx == -1));
-          if (wall) {
+        // the ghost's share: at a wall node the forward took the ghost of tap
+        // dx = -1 at x = 0 (dx = +1 at x = nx - 1) from the wall node itself, so
+        // the wall node also collects in(wall node) under that tap; the two
+        // operands are added in FP32 and rounded once
+        if ((dx == 1 && lo[b]) || (dx == -1 && hi[b])) {
+          const bf16x8 e8 = *(const bf16x8*)(&sl[lds_at<CIN>(pos[b] + 1, c)]);
 #pragma unroll
-            for (int kc = 0; kc < KC; ++kc) {
-              const bf16x8 e8 = *(const bf16x8*)(&sl[(pos[b] + 1) * LS + kc * 16 + khalf]);
-#pragma unroll
-              for (int e = 0; e < 8; ++e) bop[b][kc][e] = (bf16)((float)bop[b][kc][e] + (float)e8[e]);
-            }
-          }
+          for (int e = 0; e < 8; ++e) v[b][e] = (bf16)((float)v[b][e] + (float)e8[e]);
         }
       }
-#pragma unroll
-      for (int kc = 0; kc < KC; ++kc)
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb) {
-          const bf16x8 a = *(const bf16x8*)(&wl[buf][(mb * 32 + (lane & 31)) * LS + kc * 16 + khalf]);
-#pragma unroll
-          for (int b = 0; b < 2; ++b)
-            acc[mb][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, bop[b][kc], acc[mb][b], 0, 0, 0);
-        }
-      if (tap + 1 < NTAP) store_w(buf ^ 1);
-      __syncthreads();
     }
-    if (g + 1 < 9 && restage) {
-      sstore();
-      __syncthreads();
+  };
+  bf16x8 held[FLAT ? STEPS : 1][2];
+  auto group = [&]() {
+    bf16x8 av[3][MB], bv[FLAT ? 1 : 3][2];
+    auto fetch = [&](int s) {
+      if constexpr (!FLAT) rows_at(s, bv[s % 3]);
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb)
+        av[s % 3][mb] =
+            *(const bf16x8*)(&wl[s / KC][lds_at<CIN>(mb * 32 + (lane & 31), 2 * (s % KC) + khalf)]);
+    };
+    fetch(0);
+    fetch(1);
+#pragma unroll
+    for (int s = 0; s < STEPS; ++s) {
+      if (s + 2 < STEPS) fetch(s + 2);
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (!FLAT) at_walls(s, bv[s % 3]);
+      bf16x8 (&v)[2] = FLAT ? held[FLAT ? s : 0] : bv[FLAT ? 0 : s % 3];
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+          acc[mb][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[s % 3][mb], v[b], acc[mb][b], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  sload(0);
+#pragma unroll
+  for (int d = 0; d < 3; ++d) load_w(d, d);
+  sstore();
+#pragma unroll
+  for (int d = 0; d < 3; ++d) store_w(d);
+  __syncthreads();
+  if constexpr (FLAT) {
+#pragma unroll
+    for (int s = 0; s < STEPS; ++s) {
+      rows_at(s, held[s]);
+      at_walls(s, held[s]);
     }
   }
+#pragma unroll 1
+  for (int g = 0; g < 8; ++g) {
+    if constexpr (!FLAT) sload(g + 1);
+#pragma unroll
+    for (int d = 0; d < 3; ++d) load_w(3 * g + 3 + d, d);
+    __builtin_amdgcn_sched_barrier(0);
+    group();
+    __syncthreads();
+    if constexpr (!FLAT) sstore();
+#pragma unroll
+    for (int d = 0; d < 3; ++d) store_w(d);
+    __syncthreads();
+  }
+  group();
   // epilogue: lane holds channels co0 .. co0+3 of its node for each group g
 #pragma unroll
   for (int b = 0; b < 2; ++b) {
@@ -1082,6 +1124,8 @@ struct mclbm_nn {
   float* cond = nullptr;                // [ntubes][S] conditioning values
   float* fin = nullptr;                 // [C][n] input fields
   float* fout = nullptr;                // [C][n] predicted fields
+  uint8_t* ends = nullptr;              // [n] first / last node of its tube (bits 0, 1): flat_yz tubes
+  std::vector<uint8_t> hEnds;
 };
 
 namespace {
@@ -1106,8 +1150,9 @@ int nn_check(mclbm_nn* net, const char* what)
 }
 
 struct NNLayout {
-  size_t tubes, tile_tube, row_first, master, mom1, mom2, grad, wf, wb, bp, act, yout, dy, dyl, wpart, bpart, dpart, cond, fin, fout,
+  size_t tubes, tile_tube, row_first, master, mom1, mom2, grad, wf, wb, bp, act, yout, dy, dyl, wpart, bpart, dpart, cond, fin, fout, ends,
       total;
+  bool flat;                            // every tube one node wide in y and z, at most 2^30 nodes
   int64_t n, ntiles, nparam, nparam_p;
   int wG;
 };
@@ -1200,6 +1245,9 @@ NNLayout nn_layout(int C, int P, int S, int Ms, int depth, const int32_t* dims, 
   l.cond = take(sizeof(float) * (size_t)ntubes * (S > 0 ? S : 1));
   l.fin = take(sizeof(float) * (size_t)l.n * C);
   l.fout = take(sizeof(float) * (size_t)l.n * C);
+  l.flat = l.n <= ((int64_t)1 << 30);
+  for (int t = 0; t < ntubes; ++t) l.flat = l.flat && dims[3 * t + 1] == 1 && dims[3 * t + 2] == 1;
+  l.ends = take(l.flat ? (size_t)l.n : 0);
   l.total = off;
   return l;
 }
@@ -1236,8 +1284,14 @@ int repack(mclbm_nn* net)
 template <int CIN, int COUT, int EPI>
 void conv(mclbm_nn* net, const bf16* W, const float* b, const bf16* in, const bf16* mask, void* out)
 {
-  hipLaunchKernelGGL((k_conv<CIN, COUT, EPI>), dim3((unsigned)net->ntiles), dim3(256), 0, net->stream, net->dTubes,
-                     net->dTileTube, net->ntubes, W, b, in, mask, out);
+  // one row of all nodes where every tube is one node wide in y and z and the row's
+  // indices fit the kernel's 32 bits
+  if (net->ends)
+    hipLaunchKernelGGL((k_conv<CIN, COUT, EPI, true>), dim3(blocks_for(net->n, TILE)), dim3(256), 0, net->stream,
+                       net->dTubes, net->dTileTube, net->ntubes, net->ends, W, b, in, mask, out);
+  else
+    hipLaunchKernelGGL((k_conv<CIN, COUT, EPI, false>), dim3((unsigned)net->ntiles), dim3(256), 0, net->stream,
+                       net->dTubes, net->dTileTube, net->ntubes, nullptr, W, b, in, mask, out);
 }
 
 template <int CIN, int COUT>
@@ -1373,6 +1427,14 @@ extern "C" int mclbm_nn_create(int32_t channels, int32_t two_term, int32_t condi
   }
   net->flat_yz = true;
   for (const NTube& tb : net->hTubes) net->flat_yz = net->flat_yz && tb.ny == 1 && tb.nz == 1;
+  if (lay.flat) {
+    net->ends = (uint8_t*)(ws + lay.ends);
+    net->hEnds.assign((size_t)lay.n, 0);
+    for (const NTube& tb : net->hTubes) {
+      net->hEnds[tb.base] |= 1;
+      net->hEnds[tb.base + tb.nx - 1] |= 2;
+    }
+  }
   net->hRowFirst.resize(ntubes);
   net->nrows = 0;
   for (int t = 0; t < ntubes; ++t) {
@@ -1395,6 +1457,8 @@ extern "C" int mclbm_nn_create(int32_t channels, int32_t two_term, int32_t condi
   if (e == hipSuccess)
     e = hipMemcpyAsync(net->dRowFirst, net->hRowFirst.data(), sizeof(int32_t) * ntubes, hipMemcpyHostToDevice,
                        net->stream);
+  if (e == hipSuccess && net->ends)
+    e = hipMemcpyAsync(net->ends, net->hEnds.data(), net->hEnds.size(), hipMemcpyHostToDevice, net->stream);
   if (e == hipSuccess) {
     // parameters, moments and gradients start at zero (set_params gives the weights)
     for (float* p : {net->master, net->mom1, net->mom2, net->grad})

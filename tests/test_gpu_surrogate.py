@@ -194,6 +194,43 @@ def test_gradients_match_oracle_on_one_node_wide_tubes(env):
                     assert np.all(gw[:, :, dx] == gw[1, 1, dx]), (li, dx)
 
 
+@pytest.mark.parametrize("dims", [
+    [(255, 1, 1), (1, 1, 1), (2, 1, 1), (256, 1, 1), (300, 1, 1), (1, 1, 1)],   # across 256-node tiles, ragged end
+    [(1, 1, 1), (1, 1, 1), (1, 1, 1), (253, 1, 1)],                             # one full tile
+    [(20, 1, 1), (13, 4, 3), (1, 3, 1)],                                        # not all one node wide
+])
+def test_forward_and_gradients_where_tubes_meet_tiles(env, dims):
+    """Tubes that begin and end inside the convolution's tiles, against the oracle."""
+    depth = 3
+    p = S.he_init(C, depth, seed=19, gain=1.0)
+    p += np.random.default_rng(15).normal(0, 0.02, p.size).astype(np.float32)
+    nm = norm_arrays(1)
+    nm64 = {k: np.asarray(v, np.float32).astype(np.float64) for k, v in nm.items()}
+    net = make_net(env, depth, p, nm, dims=dims)
+    fs = [f.astype(np.float32).astype(np.float64) for f in random_fields(16, dims=dims)]
+    rng = np.random.default_rng(18)
+    tg = [(f + 0.05 * rng.normal(size=f.shape)).astype(np.float32).astype(np.float64) for f in fs]
+    w = np.linspace(0.5, 2.0, C).astype(np.float32)
+    net.zero_grad()
+    out = net.forward(flat(env, fs)).cpu().numpy()
+    loss = net.loss(flat(env, tg), w)
+    net.backward()
+    g_gpu = net.get_grads().astype(np.float64)
+    net.close()
+    for t, (f, g) in enumerate(zip(fs, split(out, dims=dims))):
+        y_ref, _, _ = S.forward(p, f, nm64, C, depth, round_bf16=True)
+        y_gpu = (g - f.astype(np.float32)) / nm64["out_scale"][:, None, None, None]
+        assert np.abs(y_gpu - y_ref).max() < 5e-3 * np.abs(y_ref).max(), t
+    L_ref, g_ref = S.loss_and_grad(p, fs, tg, nm64, C, depth, weight=w.astype(np.float64), round_bf16=True)
+    assert loss == pytest.approx(L_ref, rel=5e-3)
+    k = 0
+    for li, (o, i) in enumerate(S.layer_shapes(C, depth)):
+        for name, size in (("W", 27 * o * i), ("b", o)):
+            a, b = g_gpu[k:k + size], g_ref[k:k + size]
+            k += size
+            assert np.abs(a - b).max() < GRAD_BOUND * np.abs(b).max(), (li, name)
+
+
 def test_adam_step_matches_oracle(env):
     depth = 3
     p = S.he_init(C, depth, seed=11)
