@@ -365,156 +365,166 @@ __global__ __launch_bounds__(256, (conv_waves<CIN, COUT, EPI, FLAT>())) void k_c
 // Weight gradient: dW[tap][co][ci] = sum_nodes dY[node][co] X[node + d_tap][ci]
 // (the forward's gather: x clamped to the tube, y and z wrapped)
 // ---------------------------------------------------------------------------
-// The reduction runs over nodes, so both operands are staged transposed in LDS
-// (channel rows, node columns) for 128-node chunks; workgroup (g, (dy, dz)) sums
-// the chunks g, g + G, ... for the taps dx = -1, 0, +1 and writes its partials
-// [g][tap][COUT][CINP]. With yz_fixed >= 0 the grid has one (dy, dz) column, that
-// one: when every tube is one node wide in y and z, the y and z shifts wrap onto
-// the node itself and the nine (dy, dz) columns would sum the same products in
-// the same order, so k_wgrad_reduce reads the one for all of them. The partials
-// are then [g][dx][COUT][CINP], and nine times as many workgroups share the
-// chunks (the same buffer).
+// The reduction runs over nodes: workgroup (g, (dy, dz)) sums the 128-node chunks g, g + G, ...
+// for the taps dx = -1, 0, +1 and writes its partials [g][tap][COUT][CIN]. A chunk's
+// rows of dY and the rows node0 - 1 .. node0 + 128 of X shifted by (dy, dz) are staged in LDS as they
+// lie in memory, and the transposing LDS read gives each lane the four nodes of its
+// channel; the rows of the three taps differ by one, at a wall the tap takes the node's own
+// row, and a node outside the chunk's tube reads a row of zeros in both. The next chunk's rows are
+// loaded into registers while the current chunk's products run. Staged transposed
+// instead, with one 2-byte store per value and a copy of X per tap, the LDS stores took
+// twice the time of the products (64 x 64, 590 k nodes of 4096 tubes: 65.5 -> 36 us).
+// The bias gradient is one more product, dY with a column of ones, in the wavefronts that
+// hold the first input channels of the (0, 0) column: a pass of its own over dY and its reduction took 32 us.
+//
+// FLAT (every tube one node wide in y and z): the chunks run across the tubes as k_conv's tiles
+// do, and the y and z shifts wrap onto the node itself, so the nine (dy, dz) columns would
+// sum the same products: the grid has one, the partials are [g][dx][COUT][CIN], and nine
+// times as many workgroups share the chunks.
 constexpr int WCH = 128;   // nodes per staged chunk
 
-template <int CIN, int COUT>
-__global__ __launch_bounds__(256) void k_wgrad(const NTube* __restrict__ tubes, const int32_t* __restrict__ tile_tube,
-                                               int ntubes, int nchunks, const bf16* __restrict__ dY,
-                                               const bf16* __restrict__ X, float* __restrict__ partial,
-                                               int yz_fixed)
+// four nodes (rows r, r + 1, .. of the lane's row address) of one channel
+using i16x4 = short __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ i16x4 lds_read_tr(const bf16* p)
 {
-  constexpr int CINP = CIN < 32 ? 32 : CIN;
-  constexpr int S = WCH + 8;
-  constexpr int NB = (COUT / 32) * (CINP / 32);
-  constexpr int PW = (NB + 3) / 4;
-  // one workgroup takes the three taps dx = -1, 0, +1 of one (dy, dz): the output
-  // gradient chunk is staged once for all three, and the three shifted input
-  // windows overlap (two of them come from the cache)
-  __shared__ __attribute__((aligned(16))) bf16 dyt[COUT * S];
-  __shared__ __attribute__((aligned(16))) bf16 xt[3][CINP * S];
-  const int yz = yz_fixed >= 0 ? yz_fixed : (int)blockIdx.y, g = blockIdx.x, G = gridDim.x;
+  return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) i16x4*)p);
+}
+
+template <int CIN, int COUT, bool FLAT>
+__global__ __launch_bounds__(256, 2) void k_wgrad(const NTube* __restrict__ tubes, const int32_t* __restrict__ tile_tube,
+                                               int ntubes, int nchunks, const uint8_t* __restrict__ ends,
+                                               const bf16* __restrict__ dY, const bf16* __restrict__ X,
+                                               float* __restrict__ partial, float* __restrict__ bpart)
+{
+  static_assert(CIN % 32 == 0 && COUT % 32 == 0, "whole 32 x 32 blocks");
+  constexpr int SY = COUT + 8, SX = CIN + 8;          // LDS row strides: the 16 lanes of a read cover 32 banks once
+  constexpr int ZY = WCH, ZX = WCH + 2;               // rows of zeros
+  constexpr int NB = (COUT / 32) * (CIN / 32);
+  static_assert(NB <= 4, "one 32 x 32 block per wavefront");
+  __shared__ __attribute__((aligned(16))) bf16 ys[(WCH + 1) * SY];
+  __shared__ __attribute__((aligned(16))) bf16 xs[(WCH + 3) * SX];
+  const int yz = FLAT ? 4 : (int)blockIdx.y, g = blockIdx.x, G = gridDim.x;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int dy = yz % 3 - 1, dz = yz / 3 - 1;
-  const int tap0 = 9 * (dz + 1) + 3 * (dy + 1);   // taps tap0 + k, dx = k - 1
-  f32x16 acc[3][PW];
+  const int tap0 = FLAT ? 0 : 9 * (dz + 1) + 3 * (dy + 1);   // taps tap0 + k, dx = k - 1
+  const int mb = wave / (CIN / 32), cb = wave % (CIN / 32);
+  const bool with_bias = wave < NB && cb == 0 && yz == 4;
+  f32x16 acc[3], accb;
 #pragma unroll
-  for (int k = 0; k < 3; ++k)
-#pragma unroll
-    for (int q = 0; q < PW; ++q)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[k][q][v] = 0.f;
-  if (CIN < CINP) {
-    for (int e = threadIdx.x; e < 3 * (CINP - CIN) * S; e += 256) {
-      const int k = e / ((CINP - CIN) * S);
-      xt[k][CIN * S + e % ((CINP - CIN) * S)] = (bf16)0.f;
-    }
+  for (int v = 0; v < 16; ++v) {
+    acc[0][v] = acc[1][v] = acc[2][v] = accb[v] = 0.f;
   }
-  const int khalf = 8 * (lane >> 5);
-  // 4 * WCH staging items over 256 threads, two each: item < WCH stages dY of node
-  // item, item WCH + k WCH + i stages X of node i shifted by dx = k - 1. A chunk's
-  // items are loaded into registers while the previous chunk's MFMAs run.
-  constexpr int C8 = (COUT > CIN ? COUT : CIN) / 8;
-  bf16x8 st[2][C8];
-  auto load_items = [&](int ch) {
-    const int tile = ch >> 1;
-    const NTube tb = tube_of(tubes, tile_tube, ntubes, tile);
-    const int n_t = tb.nx * tb.ny * tb.nz;
-    const int node0 = (tile - tb.first_tile) * TILE + (ch & 1) * WCH;
+  for (int e = threadIdx.x; e < SY; e += 256) ys[ZY * SY + e] = (bf16)0.f;
+  for (int e = threadIdx.x; e < SX; e += 256) xs[ZX * SX + e] = (bf16)0.f;
+
+  // two threads stage a row, 8 of every 16 channels each; the two rows beyond the
+  // chunk's 128 are spread over the first threads (the others load theirs again)
+  const int row = (int)threadIdx.x >> 1, half = ((int)threadIdx.x & 1) * 8;
+  constexpr int XP = CIN / 8;                         // 16-byte pieces of a row of X
+  const bool extra = (int)threadIdx.x < 2 * XP;
+  const int xrow = extra ? WCH + (int)threadIdx.x / XP : row;
+  const int xc = extra ? (int)threadIdx.x % XP * 8 : half;
+  bf16x8 ry[COUT / 16], rx[CIN / 16], rx1;
+  // the first and last nodes of the x rows among the chunk's nodes, a bit per node, and
+  // the number of its nodes: of the staged chunk, and of the one in registers
+  uint64_t lo[2], hi[2];
+  int ends_n[2], count = 0, count_n = 0;
+  auto load_rows = [&](int ch) {
+    const NTube tb = FLAT ? tubes[0] : tube_of(tubes, tile_tube, ntubes, ch >> 1);
+    const int64_t base = FLAT ? 0 : tb.base;
+    const int n_t = FLAT ? (int)tb.ntot : tb.nx * tb.ny * tb.nz;
+    const int node0 = FLAT ? ch * WCH : ((ch >> 1) - tb.first_tile) * TILE + (ch & 1) * WCH;
+    count_n = min(max(n_t - node0, 0), WCH);
 #pragma unroll
-    for (int r = 0; r < 2; ++r) {
-      const int item = threadIdx.x + 256 * r;
-      const int node = node0 + (item & (WCH - 1));
-      const bool valid = node < n_t;
-      if (item < WCH) {
-#pragma unroll
-        for (int c8 = 0; c8 < COUT / 8; ++c8) {
-          if (valid) {
-            st[r][c8] = *(const bf16x8*)(dY + aidx(tb, tb.base + node, c8 * 8));
-          } else {
-#pragma unroll
-            for (int j = 0; j < 8; ++j) st[r][c8][j] = (bf16)0.f;
-          }
-        }
+    for (int h = 0; h < 2; ++h) {
+      const int p = min(node0 + 64 * h + lane, n_t - 1);
+      if constexpr (FLAT) {
+        ends_n[h] = ends[p];
       } else {
-        const int dx = item / WCH - 2;
-        int x = 0, y = 0, z = 0;
-        if (valid) {
-          x = node % tb.nx;
-          const int rr = node / tb.nx;
-          y = rr % tb.ny;
-          z = rr / tb.ny;
-        }
-        // replicate padding: x clamped to the tube; y, z wrapped
-        const int xx = x + dx < 0 ? 0 : (x + dx >= tb.nx ? tb.nx - 1 : x + dx);
-        const int64_t nb = wrap_index(tb, xx, y + dy, z + dz);
-#pragma unroll
-        for (int c8 = 0; c8 < CIN / 8; ++c8) {
-          if (valid) {
-            st[r][c8] = *(const bf16x8*)(X + aidx(tb, nb, c8 * 8));
-          } else {
-#pragma unroll
-            for (int j = 0; j < 8; ++j) st[r][c8][j] = (bf16)0.f;
-          }
-        }
+        const int x = p % tb.nx;
+        ends_n[h] = (x == 0 ? 1 : 0) | (x == tb.nx - 1 ? 2 : 0);
       }
     }
+    const int64_t ny0 = base + min(node0 + row, n_t - 1);
+#pragma unroll
+    for (int c = 0; c < COUT / 16; ++c) ry[c] = *(const bf16x8*)(dY + aidx(tb, ny0, 16 * c + half));
+    auto shifted = [&](int r) -> int64_t {
+      const int j = min(max(node0 + r - 1, 0), n_t - 1);
+      if constexpr (FLAT) return j;
+      const int q = j / tb.nx;
+      return wrap_index(tb, j % tb.nx, q % tb.ny + dy, q / tb.ny + dz);
+    };
+    const int64_t nx0 = shifted(row), nx1 = shifted(xrow);
+#pragma unroll
+    for (int c = 0; c < CIN / 16; ++c) rx[c] = *(const bf16x8*)(X + aidx(tb, nx0, 16 * c + half));
+    rx1 = *(const bf16x8*)(X + aidx(tb, nx1, xc));
   };
-  auto store_items = [&]() {
+  auto store_rows = [&]() {
 #pragma unroll
-    for (int r = 0; r < 2; ++r) {
-      const int item = threadIdx.x + 256 * r;
-      const int i = item & (WCH - 1);
-      if (item < WCH) {
+    for (int c = 0; c < COUT / 16; ++c) *(bf16x8*)(&ys[row * SY + 16 * c + half]) = ry[c];
 #pragma unroll
-        for (int c8 = 0; c8 < COUT / 8; ++c8)
+    for (int c = 0; c < CIN / 16; ++c) *(bf16x8*)(&xs[row * SX + 16 * c + half]) = rx[c];
+    if (extra) *(bf16x8*)(&xs[xrow * SX + xc]) = rx1;
+    count = count_n;
 #pragma unroll
-          for (int j = 0; j < 8; ++j) dyt[(c8 * 8 + j) * S + i] = st[r][c8][j];
-      } else {
-        const int k = item / WCH - 1;
-#pragma unroll
-        for (int c8 = 0; c8 < CIN / 8; ++c8)
-#pragma unroll
-          for (int j = 0; j < 8; ++j) xt[k][(c8 * 8 + j) * S + i] = st[r][c8][j];
-      }
+    for (int h = 0; h < 2; ++h) {
+      lo[h] = __ballot(ends_n[h] & 1);
+      hi[h] = __ballot(ends_n[h] & 2);
     }
   };
-  if (g < nchunks) load_items(g);
+  // a lane's share of the transposing read of nodes k .. k + 15: it reads the channels
+  // colb .. colb + 3 of node k + kl (and k + kl + 4) and receives its own channel, lane & 31,
+  // of the nodes k + 8 (lane >> 5) .. + 7
+  const int kl = 8 * (lane >> 5) + ((lane & 15) >> 2);
+  const int colb = 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
+  bf16x8 ones;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) ones[e] = (bf16)1.f;
+
+  if (g < nchunks) load_rows(g);
   for (int ch = g; ch < nchunks; ch += G) {
-    store_items();
+    __syncthreads();                                  // the previous chunk's reads
+    store_rows();
     __syncthreads();
-    if (ch + G < nchunks) load_items(ch + G);
+    load_rows(min(ch + G, nchunks - 1));
+    __builtin_amdgcn_sched_barrier(0);
+    if (wave < NB) {
+      for (int k0 = 0; k0 < count; k0 += 16) {
+        const uint32_t los = (uint32_t)(lo[k0 >> 6] >> (k0 & 63)), his = (uint32_t)(hi[k0 >> 6] >> (k0 & 63));
+        i16x4 a[2], b[3][2];
 #pragma unroll
-    for (int q = 0; q < PW; ++q) {
-      const int blk = wave + 4 * q;
-      if (blk < NB) {
-        const int mb = blk / (CINP / 32), cb = blk % (CINP / 32);
-#pragma unroll 2
-        for (int k0 = 0; k0 < WCH; k0 += 16) {
-          const bf16x8 a = *(const bf16x8*)(&dyt[(mb * 32 + (lane & 31)) * S + k0 + khalf]);
+        for (int h = 0; h < 2; ++h) {
+          const int k = k0 + kl + 4 * h;
+          const bool in = k < count;
+          const bool first = (los >> (kl + 4 * h)) & 1, last = (his >> (kl + 4 * h)) & 1;
+          a[h] = lds_read_tr(&ys[(in ? k : ZY) * SY + mb * 32 + colb]);
 #pragma unroll
-          for (int k = 0; k < 3; ++k) {
-            const bf16x8 b = *(const bf16x8*)(&xt[k][(cb * 32 + (lane & 31)) * S + k0 + khalf]);
-            acc[k][q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc[k][q], 0, 0, 0);
+          for (int d = 0; d < 3; ++d) {
+            const int r = in ? k + 1 + (d == 0 ? (first ? 0 : -1) : (d == 2 ? (last ? 0 : 1) : 0)) : ZX;
+            b[d][h] = lds_read_tr(&xs[r * SX + cb * 32 + colb]);
           }
         }
+        auto join = [](i16x4 p, i16x4 q) {
+          return __builtin_bit_cast(bf16x8, __builtin_shufflevector(p, q, 0, 1, 2, 3, 4, 5, 6, 7));
+        };
+        const bf16x8 av = join(a[0], a[1]);
+#pragma unroll
+        for (int d = 0; d < 3; ++d)
+          acc[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, join(b[d][0], b[d][1]), acc[d], 0, 0, 0);
+        if (with_bias) accb = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, ones, accb, 0, 0, 0);
       }
     }
-    __syncthreads();
   }
+  if (wave >= NB) return;
 #pragma unroll
-  for (int k = 0; k < 3; ++k)
+  for (int v = 0; v < 16; ++v) {
+    const int co = mb * 32 + 8 * (v / 4) + 4 * (lane >> 5) + (v % 4);
+    const int ci = cb * 32 + (lane & 31);
 #pragma unroll
-    for (int q = 0; q < PW; ++q) {
-      const int blk = wave + 4 * q;
-      if (blk >= NB) continue;
-      const int mb = blk / (CINP / 32), cb = blk % (CINP / 32);
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int row = mb * 32 + 8 * (v / 4) + 4 * (lane >> 5) + (v % 4);
-        const int col = cb * 32 + (lane & 31);
-        const size_t pt = yz_fixed >= 0 ? (size_t)g * 3 + k : (size_t)g * NTAP + tap0 + k;
-        partial[(pt * COUT + row) * CINP + col] = acc[k][q][v];
-      }
-    }
+    for (int d = 0; d < 3; ++d)
+      partial[(((size_t)g * (FLAT ? 3 : NTAP) + tap0 + d) * COUT + co) * CIN + ci] = acc[d][v];
+    if (with_bias && (lane & 31) == 0) bpart[(size_t)g * COUT + co] = accb[v];
+  }
 }
 
 // grad[tap][co][j] += sum_g partial[g][tap][co][col] over the parameters of a
@@ -524,120 +534,77 @@ __global__ __launch_bounds__(256) void k_wgrad(const NTube* __restrict__ tubes, 
 // parameters j >= C sit at column j + P. With flat != 0 (tubes one node wide in
 // y and z) the partials are [G][dx][COUTP][CINP]: each sum is formed once per dx
 // and added to the gradient of its nine taps.
-__global__ __launch_bounds__(256) void k_wgrad_reduce(const float* __restrict__ partial, int G, int COUTP,
+//
+// A workgroup takes 128 consecutive padded sums (the last one the bias gradient's), wave w the w-th of eight slices of g, two
+// sums a lane; the slices are then added in order. What bounds it is how much lies side by side
+// under one load of the 25 MB of partials: 32 sums a slice, one load in flight after another, took 22 us on 504 groups
+// of 3 x 64 x 64, 10 us so.
+constexpr int WR_SLICES = 8, WR_OUT = 128;
+
+__global__ __launch_bounds__(64 * WR_SLICES) void k_wgrad_reduce(const float* __restrict__ partial,
+                                                      const float* __restrict__ bpart, int G, int COUTP,
                                                       int CINP, int co_r, int ci_r, int C, int P,
-                                                      float* __restrict__ grad, int flat)
+                                                      float* __restrict__ grad, float* __restrict__ bgrad, int flat)
 {
-  // 32 outputs per workgroup, each summed by 8 threads over a slice of g; the
-  // slices are then added in order (flat: one output per dx, whose nine taps
-  // share the sum; else one per tap)
-  constexpr int NSL = 8;
-  __shared__ float red[NSL][32][2];
-  const int jj = threadIdx.x & 31, sl = threadIdx.x >> 5;
-  const int k = blockIdx.x * 32 + jj;
-  const int nout = (flat ? 3 : NTAP) * co_r * ci_r;
-  const int npt = flat ? 3 : NTAP;
-  float s = 0.f, s2 = 0.f;
-  int j = 0, co = 0, tap = 0;
-  if (k < nout) {
-    j = k % ci_r;
-    co = (k / ci_r) % co_r;
-    tap = k / (ci_r * co_r);                   // flat: tap = dx + 1
-    const int col = (P > 0 && j >= C) ? j + P : j;
-    const int g0 = (int)((int64_t)G * sl / NSL), g1 = (int)((int64_t)G * (sl + 1) / NSL);
-    for (int g = g0; g < g1; ++g) {
-      const size_t row = (((size_t)g * npt + tap) * COUTP + co) * CINP;
-      s += partial[row + col];
-      if (P > 0 && j < P) s2 += partial[row + C + j];
+  __shared__ float2 red[WR_SLICES][WR_OUT / 2];
+  __shared__ float total[WR_OUT];
+  const int lane = threadIdx.x & 63, sl = threadIdx.x >> 6;
+  const bool bias = blockIdx.x == gridDim.x - 1;                // COUTP <= WR_OUT sums
+  const size_t gs = bias ? COUTP : (size_t)(flat ? 3 : NTAP) * COUTP * CINP;   // weights: a multiple of WR_OUT
+  const size_t e0 = bias ? 0 : (size_t)blockIdx.x * WR_OUT;
+  const int g0 = (int)((int64_t)G * sl / WR_SLICES), g1 = (int)((int64_t)G * (sl + 1) / WR_SLICES);
+  const float* src = (bias ? bpart : partial) + e0 + min(2 * lane, (int)gs - 2);
+  float2 s = {0.f, 0.f};
+  constexpr int U = 16;                        // loads in flight; the additions in the order of g
+  int g = g0;
+  for (; g + U <= g1; g += U) {
+    float2 v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = *(const float2*)(src + (size_t)(g + u) * gs);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      s.x += v[u].x;
+      s.y += v[u].y;
     }
   }
-  red[sl][jj][0] = s;
-  red[sl][jj][1] = s2;
-  __syncthreads();
-  if (sl != 0 || k >= nout) return;
-  float t = 0.f, t2 = 0.f;
-#pragma unroll
-  for (int q = 0; q < NSL; ++q) {
-    t += red[q][jj][0];
-    t2 += red[q][jj][1];
+  for (; g < g1; ++g) {
+    const float2 v = *(const float2*)(src + (size_t)g * gs);
+    s.x += v.x;
+    s.y += v.y;
   }
-  const float v = t + t2 * (1.f / 256.f);
-  if (!flat) {
-    grad[k] += v;
+  red[sl][lane] = s;
+  __syncthreads();
+  const int k = threadIdx.x;
+  if (k < WR_OUT) {
+    float t = 0.f;
+#pragma unroll
+    for (int q = 0; q < WR_SLICES; ++q) t += ((const float*)red[q])[k];
+    total[k] = t;
+  }
+  __syncthreads();
+  if (k >= WR_OUT) return;
+  if (bias) {
+    if (k < co_r) bgrad[k] += total[k];
     return;
   }
-  for (int yz = 0; yz < 9; ++yz)               // tap 9 (dz + 1) + 3 (dy + 1) + (dx + 1)
-    grad[((size_t)(3 * yz + tap) * co_r + co) * ci_r + j] += v;
-}
-
-// Bias gradient partials: partial[tile][c] = sum over the tile's nodes of dY[node][c]
-// (C = 16, 32 or 64). Wave w takes the 16-channel chunk w % (C / 16) of every
-// (4 / (C / 16))-th group of 64 nodes starting at group w / (C / 16): each lane
-// reads the chunk's 32 contiguous bytes of its nodes (a wave covers whole
-// lines), sums them per channel, the lanes are added by a butterfly and the
-// waves of a chunk in order.
-__global__ __launch_bounds__(256) void k_bgrad(const NTube* __restrict__ tubes, const int32_t* __restrict__ tile_tube,
-                                               int ntubes, int C, const bf16* __restrict__ dY,
-                                               float* __restrict__ partial)
-{
-  __shared__ float red[4][16];
-  const int tile = blockIdx.x;
-  const NTube tb = tube_of(tubes, tile_tube, ntubes, tile);
-  const int n_t = tb.nx * tb.ny * tb.nz;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int nch = C / 16, nparts = 4 / nch;
-  const int ch = wave % nch, part = wave / nch;
-  const int t0 = (tile - tb.first_tile) * TILE;
-  float s[16];
-#pragma unroll
-  for (int k = 0; k < 16; ++k) s[k] = 0.f;
-  for (int i = part * 64 + lane; i < TILE; i += 64 * nparts) {
-    if (t0 + i < n_t) {
-      const bf16x8* src = (const bf16x8*)(dY + aidx(tb, tb.base + t0 + i, ch * 16));
-      const bf16x8 a = src[0], b = src[1];
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        s[e] += (float)a[e];
-        s[8 + e] += (float)b[e];
-      }
-    }
+  // rows of CINP sums: the block holds whole rows
+  const size_t row = (e0 + k) / CINP;
+  const int col = (int)((e0 + k) % CINP), co = (int)(row % COUTP), tap = (int)(row / COUTP);   // flat: tap = dx + 1
+  const int j = P > 0 && col >= C ? col - P : col;
+  if (co >= co_r || j >= ci_r || (P > 0 && col >= C && col < C + P)) return;
+  const float t2 = P > 0 && j < P ? total[k + C] : 0.f;
+  const float v = total[k] + t2 * (1.f / 256.f);
+  float* dst = grad + ((size_t)tap * co_r + co) * ci_r + j;
+  if (!flat) {
+    *dst += v;
+    return;
   }
+  const size_t ts = (size_t)3 * co_r * ci_r;   // tap 9 (dz + 1) + 3 (dy + 1) + (dx + 1)
+  float old[9];
 #pragma unroll
-  for (int k = 0; k < 16; ++k) {
+  for (int yz = 0; yz < 9; ++yz) old[yz] = dst[yz * ts];
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) s[k] += __shfl_xor(s[k], off, 64);
-  }
-  if (lane == 0) {
-#pragma unroll
-    for (int k = 0; k < 16; ++k) red[wave][k] = s[k];
-  }
-  __syncthreads();
-  if ((int)threadIdx.x < C) {
-    const int c = threadIdx.x;
-    float t = 0.f;
-    for (int p = 0; p < nparts; ++p) t += red[p * nch + c / 16][c % 16];
-    partial[(size_t)tile * C + c] = t;
-  }
-}
-
-// grad[c] += sum_t partial[t][c] for the real channels c < count (row stride C):
-// block c, thread i sums tiles i, i + 256, ..., then a tree in LDS; a fixed order,
-// so the result is deterministic.
-__global__ __launch_bounds__(256) void k_bgrad_reduce(const float* __restrict__ partial, int ntiles, int C,
-                                                      int count, float* __restrict__ grad)
-{
-  __shared__ float red[256];
-  const int c = blockIdx.x;
-  if (c >= count) return;
-  float s = 0.f;
-  for (int t = threadIdx.x; t < ntiles; t += 256) s += partial[(size_t)t * C + c];
-  red[threadIdx.x] = s;
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) grad[c] += red[0];
+  for (int yz = 0; yz < 9; ++yz) dst[yz * ts] = old[yz] + v;
 }
 
 // ---------------------------------------------------------------------------
@@ -1119,7 +1086,7 @@ struct mclbm_nn {
   float* wpart = nullptr;               // weight-gradient partials
   int wG = 0;                           // workgroups along the chunks (nine (dy, dz) columns each)
   int wGf = 0;                          // the same with one column (flat_yz): up to nine times wG
-  float* bpart = nullptr;               // bias-gradient partials [ntiles][WIDTH]
+  float* bpart = nullptr;               // bias-gradient partials [wG or wGf][WIDTH]
   double* dpart = nullptr;              // loss / residual partials
   float* cond = nullptr;                // [ntubes][S] conditioning values
   float* fin = nullptr;                 // [C][n] input fields
@@ -1240,7 +1207,7 @@ NNLayout nn_layout(int C, int P, int S, int Ms, int depth, const int32_t* dims, 
   off += align_up(sizeof(bf16) * (size_t)l.n * WIDTH);      // second ping-pong buffer
   l.dyl = take(sizeof(bf16) * (size_t)l.n * COUTL);
   l.wpart = take(sizeof(float) * (size_t)l.wG * NTAP * WIDTH * WIDTH);
-  l.bpart = take(sizeof(float) * (size_t)l.ntiles * WIDTH);
+  l.bpart = take(sizeof(float) * (size_t)std::min<int64_t>(2 * l.ntiles, 9 * (int64_t)l.wG) * WIDTH);
   l.dpart = take(sizeof(double) * (size_t)l.ntiles * MAXC);
   l.cond = take(sizeof(float) * (size_t)ntubes * (S > 0 ? S : 1));
   l.fin = take(sizeof(float) * (size_t)l.n * C);
@@ -1294,28 +1261,29 @@ void conv(mclbm_nn* net, const bf16* W, const float* b, const bf16* in, const bf
                        net->dTubes, net->dTileTube, net->ntubes, nullptr, W, b, in, mask, out);
 }
 
+// weight and bias gradients of a layer
 template <int CIN, int COUT>
 void wgrad(mclbm_nn* net, const bf16* dY, const bf16* X, int layer)
 {
-  constexpr int CINP = CIN < 32 ? 32 : CIN;
-  const int nchunks = (int)(2 * net->ntiles);
-  const int G = net->flat_yz ? net->wGf : net->wG;
-  hipLaunchKernelGGL((k_wgrad<CIN, COUT>), dim3(G, net->flat_yz ? 1 : NTAP / 3), dim3(256), 0, net->stream,
-                     net->dTubes, net->dTileTube, net->ntubes, nchunks, dY, X, net->wpart, net->flat_yz ? 4 : -1);
+  const bool flat = net->ends != nullptr;
+  int G;
+  if (flat) {
+    const int nchunks = blocks_for(net->n, WCH);
+    G = std::min(net->wGf, nchunks);
+    hipLaunchKernelGGL((k_wgrad<CIN, COUT, true>), dim3(G), dim3(256), 0, net->stream, net->dTubes, net->dTileTube,
+                       net->ntubes, nchunks, net->ends, dY, X, net->wpart, net->bpart);
+  } else {
+    G = net->wG;
+    hipLaunchKernelGGL((k_wgrad<CIN, COUT, false>), dim3(G, NTAP / 3), dim3(256), 0, net->stream, net->dTubes,
+                       net->dTileTube, net->ntubes, (int)(2 * net->ntiles), nullptr, dY, X, net->wpart, net->bpart);
+  }
   // only the real channels have parameters (the padded ones stay zero)
   const int co_r = net->out_r[layer], ci_r = net->in_r[layer];
-  const int n = (net->flat_yz ? 3 : NTAP) * co_r * ci_r;
-  hipLaunchKernelGGL(k_wgrad_reduce, dim3(blocks_for(n, 32)), dim3(256), 0, net->stream, net->wpart, G,
-                     COUT, CINP, co_r, ci_r, layer == 0 ? net->C : ci_r, layer == 0 ? net->P : 0,
-                     net->grad + net->w_off[layer], net->flat_yz ? 1 : 0);
-}
-
-void bgrad(mclbm_nn* net, const bf16* dY, int C, int layer)
-{
-  hipLaunchKernelGGL(k_bgrad, dim3((unsigned)net->ntiles), dim3(256), 0, net->stream, net->dTubes, net->dTileTube,
-                     net->ntubes, C, dY, net->bpart);
-  hipLaunchKernelGGL(k_bgrad_reduce, dim3((unsigned)net->out_r[layer]), dim3(256), 0, net->stream, net->bpart,
-                     (int)net->ntiles, C, net->out_r[layer], net->grad + net->b_off[layer]);
+  const int n = (flat ? 3 : NTAP) * COUT * CIN;
+  static_assert(WR_OUT % CIN == 0 && COUT * CIN % WR_OUT == 0 && COUT <= WR_OUT, "whole rows per workgroup");
+  hipLaunchKernelGGL(k_wgrad_reduce, dim3(n / WR_OUT + 1), dim3(64 * WR_SLICES), 0, net->stream, net->wpart,
+                     net->bpart, G, COUT, CIN, co_r, ci_r, layer == 0 ? net->C : ci_r, layer == 0 ? net->P : 0,
+                     net->grad + net->w_off[layer], net->grad + net->b_off[layer], flat ? 1 : 0);
 }
 
 }  // namespace
@@ -1624,17 +1592,14 @@ extern "C" int mclbm_nn_backward(mclbm_nn* net)
   const int D = net->depth;
   // last layer: dW from dyl and act[D-1]; then the gradient of act[D-1]
   wgrad<WIDTH, COUTL>(net, net->dyl, net->act[D - 1], D - 1);
-  bgrad(net, net->dyl, COUTL, D - 1);
   conv<COUTL, WIDTH, 2>(net, net->wb[D - 1], nullptr, net->dyl, net->act[D - 1], net->dy[0]);
   int cur = 0;
   for (int k = D - 2; k >= 1; --k) {
     wgrad<WIDTH, WIDTH>(net, net->dy[cur], net->act[k], k);
-    bgrad(net, net->dy[cur], WIDTH, k);
     conv<WIDTH, WIDTH, 2>(net, net->wb[k], nullptr, net->dy[cur], net->act[k], net->dy[cur ^ 1]);
     cur ^= 1;
   }
   wgrad<CIN0, WIDTH>(net, net->dy[cur], net->act[0], 0);
-  bgrad(net, net->dy[cur], WIDTH, 0);
   return nn_check(net, "mclbm_nn_backward");
 }
 
