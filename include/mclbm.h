@@ -293,7 +293,7 @@ int mclbm_kernel_stats(mclbm_ctx *c, int32_t kernel, double *total_ms, int64_t *
 typedef struct {
   int32_t variant;      /* occupancy variant of the moments kernel, and of the fused
                            collide kernel (split = 0), 0 or 1                           */
-  int32_t swizzle;      /* 1: each XCD takes a contiguous run of blocks                  */
+  int32_t swizzle;      /* 1: each XCD takes a contiguous run of blocks; 0: short runs in turn */
   int32_t order;        /* 0: tubes in the given order; 1: longest tube first            */
   int32_t graph_steps;  /* 0: launch each kernel of each step; K > 0 (even): replay a
                            HIP graph of K captured steps (not while timing is enabled)   */
