@@ -339,3 +339,19 @@ def test_block_shapes_are_bitwise_equal_single_contexts(mc, prec):
             s.close()
         for shape in range(1, 6):
             assert outs[shape] == outs[0], (params["wall_x"], shape)
+
+
+@pytest.mark.parametrize("dims", [(64, 32, 24), (37, 53, 26), (32, 37, 41)])   # 192, 200 and 190 blocks
+def test_block_numberings_are_bitwise_equal(mc, dims):
+    """Blocks are dealt to the eight XCDs in runs of 24: one whole deal, one and a
+    ragged rest, less than one; against one contiguous run per XCD."""
+    params, f = W.shear_layer(nx=dims[0], ny=dims[1], nz=dims[2])
+    out = []
+    for swizzle in (0, 1):
+        s = mc.Sim(params, mc.MCLBM_FP32)
+        s.set_launch(swizzle=swizzle)
+        s.init_fields(**f)
+        s.step(3)
+        out.append(bytes(s.save()))
+        s.close()
+    assert out[0] == out[1]

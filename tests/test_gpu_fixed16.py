@@ -157,3 +157,23 @@ def test_value_out_of_range_is_an_error(mc):
     s.step(40)
     assert np.isfinite(s.conservation()).all()
     s.close()
+
+
+@pytest.mark.parametrize("nx,ny,nz", [(16, 16, 16), (16, 16, 17), (37, 53, 26)])   # 16, 17 and 200 blocks
+def test_initial_ranges_see_the_last_node(mc, nx, ny, nz):
+    """The range measurement takes 16 blocks to a workgroup: the grid's extreme value
+    sits at its last node, and no stored value may pass half of its range."""
+    params, f = W.shear_layer(nx=nx, ny=ny, nz=nz)
+    f["p"] = np.array(f["p"])
+    f["p"].reshape(-1)[-1] *= 1.2
+    s = mc.Sim(params, mc.MCLBM_I16)
+    s.init_fields(**f)
+    _, vals = decode_checkpoint(s.save())
+    p = s.read_moments()["p"].reshape(-1)
+    s.close()
+    v = vals.reshape(vals.shape[0], 27, -1).astype(np.int64)
+    for l in range(v.shape[0]):
+        for k in range(8):
+            assert np.abs(v[l][_CLS == k]).max() <= 16400, (l, k)
+    ref = f["p"].reshape(-1)[-1]
+    assert abs(p[-1] - ref) < 5e-4 * ref
