@@ -366,7 +366,19 @@ def surrogate_bench(train_iters: int = 72000):
 
     t0 = time.perf_counter()
     train_tubes = W.tube_ensemble(ntubes=4096, ny=1, nz=1, seed=11286)
-    snaps, dims = SG.trajectories(train_tubes, K=100, nsnap=50)
+    # A tube at the edge of the lattice's stable range amplifies the storage rounding of its
+    # first steps 30-fold every 20 steps: in FP32 storage most runs of tube 2110 from initial
+    # pressures 1e-9 apart leave the range by step 100 (in FP64 none), so whether it is
+    # usable hangs on the last bits of the kernels. Such tubes are left out and reported.
+    left_out = []
+    try:
+        snaps, dims = SG.trajectories(train_tubes, K=100, nsnap=50)
+    except ValueError as err:
+        if not getattr(err, "tubes", None):
+            raise
+        left_out = err.tubes
+        train_tubes = [t for k, t in enumerate(train_tubes) if k not in left_out]
+        snaps, dims = SG.trajectories(train_tubes, K=100, nsnap=50)
     M = 3
     C = SG.channels(M)
     st = SG.channel_stats(snaps, dims, M)
@@ -420,6 +432,7 @@ def surrogate_bench(train_iters: int = 72000):
     achieved = flops / (ms_fwd * 1e-3) / 1e12
     train_flops = 3 * fpn * n_train
     return {
+        "train_tubes_left_out": left_out,
         "workload": "train: 4096 ternary tubes L~U{32..256}x1x1, 50 snapshots every 100 steps; "
                     "apply: 8 held-out ternary tubes 128x32x32, one 100-step hop from t0 = 0, 1000, 3000, 4000, 6000, 8000",
         "network": {"layers": SG.DEPTH, "width": 64, "kernel": "3x3x3", "params": int(params.size),

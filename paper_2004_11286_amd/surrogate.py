@@ -60,7 +60,9 @@ def trajectories(tubes: list, K: int = K_DEFAULT, nsnap: int = 50, precision: in
             bad.append(t)
         off += n
     if bad:
-        raise ValueError(f"tubes {bad} became non-finite within {K * nsnap} steps; leave them out of the ensemble")
+        err = ValueError(f"tubes {bad} became non-finite within {K * nsnap} steps; leave them out of the ensemble")
+        err.tubes = bad
+        raise err
     return snaps, dims
 
 
