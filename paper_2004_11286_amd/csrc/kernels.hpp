@@ -187,7 +187,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(collide_p
 // as the lower one: below it the compiler's scheduler gives up loads in flight to reach
 // a register count that lets one more wave in, and puts a wait after each load (the
 // fixed-point k_collide_fg on 190 x 164 x 156 nodes at two waves: 599 us without the
-// bound, 447 us with it). 16-bit state passes
+// bound, 424 us with it). 16-bit state passes
 // keep their registers low by themselves (four waves) and are left free.
 // Three stored species or more in FP64 arithmetic, and two with FP64 storage too, take
 // one wave and the whole register file (four species at two waves spill 288 bytes per
@@ -224,14 +224,19 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(state_wav
 // Occupancy targets of k_collide_fg: two waves per SIMD (variant 0; about 230
 // registers), or no bound on the registers (variant 1: one wave per SIMD).
 // 16-bit floating point fits three waves by itself and is left free above (131 x 97 x
-// 89: 96 us, held to two waves 103 us).
+// 89: 96 us, held to two waves 103 us), except at reflecting walls, whose selections
+// need two waves' registers (160 x 150 x 140 with x walls, BF16: 275 us, left free 442 us;
+// FP16 282 and 360 us).
 template <int V>
 constexpr int collide_fg_waves() { return V == 0 ? 2 : 1; }
-template <typename S, int V>
-constexpr int collide_fg_waves_max() { return sizeof(S) == 2 && !is_fixed16<S>() ? 8 : collide_fg_waves<V>(); }
+template <typename S, int W, int V>
+constexpr int collide_fg_waves_max()
+{
+  return sizeof(S) == 2 && !is_fixed16<S>() && !reflecting(W) ? 8 : collide_fg_waves<V>();
+}
 
 template <typename S, typename R, typename Rec, int M, int W, int V, bool WEAK>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(collide_fg_waves<V>(), collide_fg_waves_max<S, V>()))) void k_collide_fg(
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(collide_fg_waves<V>(), collide_fg_waves_max<S, W, V>()))) void k_collide_fg(
     const Params<R>* __restrict__ P, Launch Ln, const S* __restrict__ src, S* __restrict__ dst,
     const Rec* __restrict__ rec, const Rec* __restrict__ G, StepNo sn)
 {

@@ -794,7 +794,7 @@ __host__ __device__ __forceinline__ void range_check(const Params<R>& P, const R
 // store per direction. Through the directions' own resources the reflected lanes needed
 // a branch and a second, global store in each of the 18 directions that cross a wall;
 // in the tubes nearly every wavefront holds a wall node (512 tubes of 32..256 x 16 x 16,
-// M = 3, FP32: k_collide_fg 5.31 -> 2.19 ms). The offsets need Q n values below 2^32
+// M = 3, FP32: k_collide_fg 5.31 -> 2.01 ms). The offsets need Q n values below 2^32
 // bytes; larger tubes store through 64-bit addresses.
 template <typename S, typename R, int BC>
 __host__ __device__ __forceinline__ void push_all(const Params<R>& P, S* __restrict__ dst, const Nbr& b, int l,
@@ -1546,8 +1546,8 @@ enum {
 // node issued at the start. Two with 4-byte storage: LDS, 55 KB per workgroup, two
 // workgroups per compute unit. The rest read them a second time: eight waves' values
 // of all lattices do not stay in an XCD's 4 MB of L2, so the second read costs
-// nearly a first one (512 ternary tubes: 3.05 ms, read twice 3.39 ms; weak coupling,
-// 1.5 M nodes: 212 us, read twice 234 us; jets 200 x 400, M = 4: 36 us against 41 us).
+// nearly a first one (512 ternary tubes: 2.73 ms, read twice 3.39 ms; weak coupling,
+// 1.5 M nodes: 208 us, read twice 234 us; jets 200 x 400, M = 4: 36 us against 41 us).
 enum { HOLD_REG, HOLD_LDS, HOLD_NONE };
 template <typename S, typename R, int M, bool WEAK>
 constexpr int hold_mode()
