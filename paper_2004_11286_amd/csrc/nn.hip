@@ -535,10 +535,11 @@ __global__ __launch_bounds__(256, 2) void k_wgrad(const NTube* __restrict__ tube
 // y and z) the partials are [G][dx][COUTP][CINP]: each sum is formed once per dx
 // and added to the gradient of its nine taps.
 //
-// A workgroup takes 128 consecutive padded sums (the last one the bias gradient's), wave w the w-th of eight slices of g, two
-// sums a lane; the slices are then added in order. What bounds it is how much lies side by side
-// under one load of the 25 MB of partials: 32 sums a slice, one load in flight after another, took 22 us on 504 groups
-// of 3 x 64 x 64, 10 us so.
+// A workgroup takes 128 consecutive padded sums (the last one the bias gradient's), wave w
+// the w-th of eight slices of g, two sums a lane; the slices are then added in order. What
+// bounds it is how much of the 25 MB of partials lies side by side under one load: 32 sums
+// a slice, one load in flight after another, took 22 us on 504 groups of 3 x 64 x 64,
+// 10 us so.
 constexpr int WR_SLICES = 8, WR_OUT = 128;
 
 __global__ __launch_bounds__(64 * WR_SLICES) void k_wgrad_reduce(const float* __restrict__ partial,
@@ -996,25 +997,31 @@ __device__ inline int tied_column(int i, int IN, int C, int P, float& factor)
   return i - P < IN ? i - P : -1;
 }
 
-// BF16 copies of a layer's weights: forward layout [tap][OUTP][INP] (padding
-// zero) and backward-input layout [tap][INP][OUTP].
-__global__ void k_pack_w(const float* __restrict__ w, int OUT, int IN, int OUTP, int INP, int C, int P,
-                         bf16* __restrict__ wf, bf16* __restrict__ wb)
-{
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= NTAP * OUTP * INP) return;
-  const int i = k % INP, o = (k / INP) % OUTP, tap = k / (INP * OUTP);
-  float factor;
-  const int src = tied_column(i, IN, C, P, factor);
-  const float v = (o < OUT && src >= 0) ? w[((size_t)tap * OUT + o) * IN + src] * factor : 0.f;
-  wf[k] = (bf16)v;
-  if (wb) wb[((size_t)tap * INP + i) * OUTP + o] = (bf16)v;
-}
+// BF16 copies of the layers' weights: forward layout [tap][OUTP][INP] (padding zero) and
+// backward-input layout [tap][INP][OUTP]; FP32 copies of the biases, padded. Block row y
+// takes layer y: the copies follow every optimiser step, and twelve launches of 1 to 3 us each
+// for six layers, one after another, cost a training iteration of 4096 tubes 16 us more (1.61 -> 1.59 ms).
+struct PackLayer {
+  const float *w, *b;
+  int OUT, IN, OUTP, INP, C, P;
+  bf16 *wf, *wb;
+  float* bp;
+};
+constexpr int MAX_DEPTH = 16;
+struct PackLayers { PackLayer l[MAX_DEPTH]; };
 
-__global__ void k_pack_b(const float* __restrict__ b, int OUT, int OUTP, float* __restrict__ bp)
+__global__ __launch_bounds__(256) void k_pack(PackLayers layers)
 {
-  const int k = threadIdx.x;
-  if (k < OUTP) bp[k] = k < OUT ? b[k] : 0.f;
+  const PackLayer& L = layers.l[blockIdx.y];
+  const int k = blockIdx.x * 256 + threadIdx.x;
+  if (k < L.OUTP) L.bp[k] = k < L.OUT ? L.b[k] : 0.f;
+  if (k >= NTAP * L.OUTP * L.INP) return;
+  const int i = k % L.INP, o = (k / L.INP) % L.OUTP, tap = k / (L.INP * L.OUTP);
+  float factor;
+  const int src = tied_column(i, L.IN, L.C, L.P, factor);
+  const float v = (o < L.OUT && src >= 0) ? L.w[((size_t)tap * L.OUT + o) * L.IN + src] * factor : 0.f;
+  L.wf[k] = (bf16)v;
+  if (L.wb) L.wb[((size_t)tap * L.INP + i) * L.OUTP + o] = (bf16)v;
 }
 
 // Sum of squares of g[0..n) in FP64, one partial per block (grid-stride, fixed order).
@@ -1150,7 +1157,7 @@ int validate_nn(int C, int P, int S, int Ms, int depth, const int32_t* dims, int
           "channels + two_term + conditioning <= 32";
     return MCLBM_EARG;
   }
-  if (depth < 2 || depth > 16) { err = "depth must be in 2..16"; return MCLBM_EARG; }
+  if (depth < 2 || depth > MAX_DEPTH) { err = "depth must be in 2..16"; return MCLBM_EARG; }
   if (!dims || ntubes < 1) { err = "tube dimensions must be given"; return MCLBM_EARG; }
   int64_t tiles = 0;
   for (int t = 0; t < ntubes; ++t) {
@@ -1237,15 +1244,16 @@ int tube_sums(mclbm_nn* net, int nv, std::vector<double>& out)
 
 int repack(mclbm_nn* net)
 {
+  PackLayers layers{};
+  int most = 0;
   for (int k = 0; k < net->depth; ++k) {
-    const int total = NTAP * net->out_p[k] * net->in_p[k];
-    hipLaunchKernelGGL(k_pack_w, dim3(blocks_for(total, 256)), dim3(256), 0, net->stream, net->master + net->w_off[k],
-                       net->out_r[k], net->in_r[k], net->out_p[k], net->in_p[k], k == 0 ? net->C : net->in_r[k],
-                       k == 0 ? net->P : 0, net->wf[k], k > 0 ? net->wb[k] : nullptr);
-    hipLaunchKernelGGL(k_pack_b, dim3(1), dim3(64), 0, net->stream, net->master + net->b_off[k], net->out_r[k],
-                       net->out_p[k], net->bp[k]);
+    layers.l[k] = {net->master + net->w_off[k], net->master + net->b_off[k], net->out_r[k], net->in_r[k],
+                   net->out_p[k], net->in_p[k], k == 0 ? net->C : net->in_r[k], k == 0 ? net->P : 0,
+                   net->wf[k], k > 0 ? net->wb[k] : nullptr, net->bp[k]};
+    most = std::max(most, NTAP * net->out_p[k] * net->in_p[k]);
   }
-  return nn_check(net, "k_pack_w");
+  hipLaunchKernelGGL(k_pack, dim3(blocks_for(most, 256), (unsigned)net->depth), dim3(256), 0, net->stream, layers);
+  return nn_check(net, "k_pack");
 }
 
 template <int CIN, int COUT, int EPI>
