@@ -366,7 +366,12 @@ __host__ __device__ __forceinline__ void species_present(const Params<R>& P, con
 // then keep a stale value. (The four-species FP64 state pass at one wave per SIMD did so
 // after the branches on absent species: the populations of nodes with an absent species
 // came out 1e-7 off.) So absence enters as a factor 1 or 0 here (MASK: FP64 and FP32
-// storage), and the streaming selects its offsets with masks (push_all).
+// storage), and the streaming selects its offsets with masks (push_all). 16-bit storage keeps
+// the selection, on which its kernels do branch: without the branches the compiler fuses other
+// multiplications and additions, and stochastic rounding turns a last bit into another
+// trajectory. In the code built now no block of a step kernel writes a vector register before
+// its lanes are on again, in any storage, and each path and variant is compared with the
+// oracle where species are absent from a part of every wavefront.
 template <typename R, int M, bool MASK>
 __host__ __device__ __forceinline__ void friction_matrix(const Params<R>& P, const Mix<R, M>& s, R Pk,
                                                 const bool present[M], R K[M][M])
