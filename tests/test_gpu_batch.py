@@ -385,3 +385,49 @@ def test_walls_beyond_32_bit_lattice_offsets(mc):
     errs = field_errors({k: np.asarray(large[k])[..., :4, :4, :] for k in FIELDS}, small)
     for k in FIELDS:
         assert errs[k] < 1e-12, (k, errs[k])
+
+
+@pytest.mark.parametrize("kind", ["walls", "walls_slip", "slip", "jets"])
+def test_reflections_beyond_32_bit_lattice_offsets(mc, kind):
+    """The 64-bit store path of every reflecting boundary with all three coordinates at work: a small
+    grid whose random state fills the whole of it, and that grid repeated along its periodic
+    directions (y and z; z alone between free-slip walls and outlets) until a lattice passes 2^32 bytes.
+    Every repetition must be the small grid's: among each other bit for bit, and to the FP64 bound of
+    the parity tests against the small grid (the reference populations of the two grids are those of
+    their mean states, whose sums differ in the last bits)."""
+    import torch
+
+    nx, ny, nz = (200, 8, 4) if kind == "walls" else (120, 36, 4)
+    (params, _), = W.tube_ensemble(ntubes=1, ny=ny, nz=nz, lmin=nx, lmax=nx, seed=9)
+    P0 = params["P0"]
+    X0 = [0.3, 0.3, 0.4]
+    params = dict(params, wall_x=0 if kind == "slip" else 1, wall_y=int(kind in ("slip", "walls_slip")))
+    if kind == "jets":
+        params.update(wall_x=3, wall_y=2, nozzle=(5, 29), inlet=np.array([0.2, 0.3, 0.5, P0, 0.31, 0.03, 0.01, -0.01]),
+                      inlet_right=np.array([0.35, 0.25, 0.4, P0, 0.3, -0.03, 0.0, 0.01]))
+    f = W.random_near_equilibrium(params, nx, ny, nz, seed=31, X0=X0, p0=P0, T0=0.3, amp=0.02, uamp=0.02)
+    need = 2 ** 32 // (27 * 8 * nx * ny * nz) + 1
+    ry = 16 if kind == "walls" else 1
+    rz = -(-need // ry)
+    big = dict(params, ny=ny * ry, nz=nz * rz)
+    assert 27 * 8 * nx * big["ny"] * big["nz"] >= 2 ** 32 > 27 * 8 * nx * ny * nz
+
+    def run(p, reps):
+        g = {k: torch.as_tensor(np.asarray(v), device="cuda") for k, v in f.items()}
+        g = {k: v.repeat(*([1] * (v.dim() - 3)), *reps, 1).contiguous() for k, v in g.items()}
+        s = mc.Sim(p, mc.MCLBM_FP64)
+        s.init_fields(**g)
+        del g
+        s.step(3)
+        m = s.read_moments(on_device=True)
+        s.close()
+        return m
+
+    small, large = run(params, (1, 1)), run(big, (rz, ry))
+    for k in FIELDS:
+        a = small[k]
+        b = large[k].reshape(tuple(a.shape[:-3]) + (rz, nz, ry, ny, nx))
+        first = b[..., :1, :, :1, :, :]
+        assert torch.equal(b, first.expand_as(b)), k
+        err = (first.reshape(a.shape) - a).abs().max() / max(float(a.abs().max()), 1e-3 if k == "u" else 0.0)
+        assert float(err) < 1e-12, (k, float(err))
