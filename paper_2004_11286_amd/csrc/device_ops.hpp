@@ -133,4 +133,13 @@ __device__ inline void stream_store(T* p, T v) { __builtin_nontemporal_store(v, 
 // above it, which bounds the loads (and registers) a thread keeps in flight.
 __device__ inline void lattice_barrier() { __asm__ __volatile__("" ::: "memory"); }
 
+// A value whose origin the compiler may no longer see: what is computed from it is computed
+// anew, not kept in registers from an earlier use of the value it was copied from.
+template <typename T>
+__device__ __forceinline__ T fresh(T v)
+{
+  __asm__ __volatile__("" : "+v"(v));
+  return v;
+}
+
 }  // namespace mclbm

@@ -801,7 +801,14 @@ __host__ __device__ __forceinline__ void range_check(const Params<R>& P, const R
 // in the tubes nearly every wavefront holds a wall node (512 tubes of 32..256 x 16 x 16,
 // M = 3, FP32: k_collide_fg 5.31 -> 2.01 ms). The offsets need Q n values below 2^32
 // bytes; larger tubes store through 64-bit addresses.
-template <typename S, typename R, int BC>
+//
+// FRESH: the offsets are computed again for each lattice. They are the same for all lattices of
+// a node, and left to itself the compiler keeps them in about 30 registers from the first
+// lattice's stores to the last one's, through the collisions in between. The 16-bit state
+// passes of three stored species fell to one wave per SIMD or spilled for them (x walls, 131 x 97 x
+// 71, M = 4: the FP16 state pass 0.204 -> 0.145 ms, the fixed-point one 0.417 -> 0.186 ms), and FP32 and
+// FP64 gain too (free-slip walls, M = 2, FP32: a step 0.214 -> 0.201 ms).
+template <typename S, typename R, int BC, bool FRESH>
 __host__ __device__ __forceinline__ void push_all(const Params<R>& P, S* __restrict__ dst, const Nbr& b, int l,
                                                   int64_t node, const S (&v)[Q])
 {
@@ -813,6 +820,12 @@ __host__ __device__ __forceinline__ void push_all(const Params<R>& P, S* __restr
   } else {
     constexpr bool XREF = xbc(BC) == BC_WALLS || xbc(BC) == BC_JETS;
     S* lat = dst + (size_t)l * Q * P.n;
+    uint32_t bx[3] = {b.x[0], b.x[1], b.x[2]}, self = (uint32_t)node;
+    if constexpr (FRESH) {
+#pragma unroll
+      for (int c = 0; c < 3; ++c) bx[c] = fresh(bx[c]);
+      self = fresh(self);
+    }
     // all ones in the lanes that touch an end: the offsets are selected without branches
     auto mask = [](bool c) -> uint32_t { return c ? ~0u : 0u; };
     const uint32_t xm[2] = {mask(b.lo), mask(b.hi)}, ym[2] = {mask(b.ylo), mask(b.yhi)};
@@ -832,12 +845,12 @@ __host__ __device__ __forceinline__ void push_all(const Params<R>& P, S* __restr
         const U mm = (U)(int64_t)(int32_t)m;
         return (a & mm) | (o & ~mm);
       };
-      const U x = b.x[c + 1] * u, y = b.y[e + 1] * u, z = b.z[cz(i) + 1] * u;
+      const U x = bx[c + 1] * u, y = b.y[e + 1] * u, z = b.z[cz(i) + 1] * u;
       U o = x + y + z + (U)i * nu;
       if ((BC & BC_YSLIP) && e) o = sel(ym[(e + 1) / 2], x + b.y[1] * u + z + (U)(i - 6 * e) * nu, o);
       if (XREF && c) {
-        if constexpr (xbc(BC) == BC_WALLS) o = sel(xm[(c + 1) / 2], (U)(uint32_t)node * u + (U)opp(i) * nu, o);
-        else o = sel(xm[(c + 1) / 2] & wall[e + 1], b.x[1] * u + y + z + (U)(i - 18 * c) * nu, o);
+        if constexpr (xbc(BC) == BC_WALLS) o = sel(xm[(c + 1) / 2], (U)self * u + (U)opp(i) * nu, o);
+        else o = sel(xm[(c + 1) / 2] & wall[e + 1], bx[1] * u + y + z + (U)(i - 18 * c) * nu, o);
       }
       return o;
     };
@@ -847,7 +860,7 @@ __host__ __device__ __forceinline__ void push_all(const Params<R>& P, S* __restr
       for (int i = 0; i < Q; ++i) {
         if ((XREF && cx(i)) || ((BC & BC_YSLIP) && cy(i))) buf_store_at<S>(lat, Q * nu, offset(i, u, nu), v[i]);
         else
-          buf_store_at<S>(lat, Q * nu, (b.x[cx(i) + 1] + b.y[cy(i) + 1] + b.z[cz(i) + 1]) * u, v[i], (uint32_t)i * nu);
+          buf_store_at<S>(lat, Q * nu, (bx[cx(i) + 1] + b.y[cy(i) + 1] + b.z[cz(i) + 1]) * u, v[i], (uint32_t)i * nu);
       }
     } else {
 #pragma unroll
@@ -855,6 +868,15 @@ __host__ __device__ __forceinline__ void push_all(const Params<R>& P, S* __restr
     }
   }
 }
+
+// Where the offsets are computed for each lattice (FRESH above): at x walls and free-slip y
+// walls. Not at the jets, whose offsets take more to compute than they free (FP32, M = 2 and 4 on
+// 131 x 97 x 71 nodes: 1.3 and 1.6% slower with it), and not in the three-pass step of two
+// species with C_v(T), which has registers left (FP64, all walls: 3% slower). k_collide_fg
+// holds two lattices only and takes it in FP64 arithmetic alone: FP32 arithmetic (16-bit storage among
+// it) has registers left there too (fixed point, x walls, M = 2: a step 0.167 ms, with it 0.171 ms).
+template <int M, int BC, bool CVT>
+constexpr bool fresh_offsets() { return reflecting(BC) && xbc(BC) != BC_JETS && !(CVT && M == 2); }
 
 // Load the Q stored values of one lattice of a node into v (lat: the lattice's
 // first direction array), all issued before any is used: the compiler barrier
@@ -1140,7 +1162,7 @@ __host__ __device__ __forceinline__ void species_relax(const Params<R>& P, const
   // the collision conserves rho_a: the rest population takes the defect of
   // the arithmetic and of the other 26 values' rounding to storage
   v[13] = to_store<S, R>(P, a, 13, t0 - s0, rng);
-  push_all<S, R, BC>(P, dst, b, a, node, v);
+  push_all<S, R, BC, fresh_offsets<M, BC, CVT>()>(P, dst, b, a, node, v);
   range_check<S, R>(P, rng);
 }
 
@@ -1149,7 +1171,7 @@ __host__ __device__ __forceinline__ void species_relax(const Params<R>& P, const
 // isotropy correction X_a = -d_a G_a (eq Xalpha). The rounding defect of mass and
 // momentum goes to the rest and face populations, which carry no other moment up
 // to second order.
-template <typename S, typename R, int BC>
+template <typename S, typename R, int BC, bool FRESH>
 __host__ __device__ __forceinline__ void momentum_relax(const Params<R>& P, int LF, R rho, const R (&u)[3], R theta,
                                                         R omega, const R (&Xc)[3], S (&v)[Q], S* __restrict__ dst,
                                                         const Nbr& b, int64_t node, uint32_t step)
@@ -1233,7 +1255,7 @@ __host__ __device__ __forceinline__ void momentum_relax(const Params<R>& P, int 
   }
   restore_faces<S, R>(P, LF, face, t1, s1, s0, v, rng);
   v[13] = to_store<S, R>(P, LF, 13, t0 - s0, rng);
-  push_all<S, R, BC>(P, dst, b, LF, node, v);
+  push_all<S, R, BC, FRESH>(P, dst, b, LF, node, v);
   range_check<S, R>(P, rng);
 }
 
@@ -1243,7 +1265,7 @@ __host__ __device__ __forceinline__ void momentum_relax(const Params<R>& P, int 
 // no pole at omega = omega_1; dq = (omega - omega_1)(q - q^eq - u.(P - P^eq))
 // + omega_1 rho sum_a H_a Y_a V_a + (2 - omega_1)/2 P sum_a H_a d Y_a is formed
 // by the caller. H is the mixture enthalpy, theta = R T.
-template <typename S, typename R, int BC>
+template <typename S, typename R, int BC, bool FRESH>
 __host__ __device__ __forceinline__ void energy_relax(const Params<R>& P, int LG, R rho, const R (&u)[3], R usq,
                                                       R theta, R H, R omega, const R (&dq)[3], S (&v)[Q],
                                                       S* __restrict__ dst, const Nbr& b, int64_t node, uint32_t step)
@@ -1320,7 +1342,7 @@ __host__ __device__ __forceinline__ void energy_relax(const Params<R>& P, int LG
   }
   // the collision conserves rho E: the rest population takes the defect
   v[13] = to_store<S, R>(P, LG, 13, t0 - s0, rng);
-  push_all<S, R, BC>(P, dst, b, LG, node, v);
+  push_all<S, R, BC, FRESH>(P, dst, b, LG, node, v);
   range_check<S, R>(P, rng);
 }
 
@@ -1478,7 +1500,7 @@ __host__ __device__ __forceinline__ void collide_node(const Params<R>& P, const 
   if constexpr (PART != 1) {
     S v[Q];
     load(LF, v);
-    momentum_relax<S, R, BC>(P, LF, rho, s.u, theta, omega, Xc, v, dst, b, node, step);
+    momentum_relax<S, R, BC, fresh_offsets<M, BC, CVT>()>(P, LF, rho, s.u, theta, omega, Xc, v, dst, b, node, step);
     lattice_barrier();
   }
 
@@ -1521,7 +1543,7 @@ __host__ __device__ __forceinline__ void collide_node(const Params<R>& P, const 
     }
     S v[Q];
     load(LG, v);
-    energy_relax<S, R, BC>(P, LG, rho, s.u, s.usq, theta, H, omega, dq, v, dst, b, node, step);
+    energy_relax<S, R, BC, fresh_offsets<M, BC, CVT>()>(P, LG, rho, s.u, s.usq, theta, H, omega, dq, v, dst, b, node, step);
   }
 }
 
@@ -1861,9 +1883,9 @@ __host__ __device__ __forceinline__ void fg_collide_node(const Params<R>& P, con
     const R qn = q[k] - hyd * rho * u[k] - up;
     dq[k] = (omega - omega1) * qn + omega1 * rho * T * (EARLY ? hyv[k] : get(REC2_HYV + k)) + R(0.5) * (R(2) - omega1) * Pp * T * gcp[k];
   }
-  momentum_relax<S, R, BC>(P, LF, rho, u, theta, omega, Xc, vf, dst, b, node, step);
+  momentum_relax<S, R, BC, fresh_offsets<M, BC, false>() && sizeof(R) == 8>(P, LF, rho, u, theta, omega, Xc, vf, dst, b, node, step);
   lattice_barrier();
-  energy_relax<S, R, BC>(P, LG, rho, u, usq, theta, H, omega, dq, vg, dst, b, node, step);
+  energy_relax<S, R, BC, fresh_offsets<M, BC, false>() && sizeof(R) == 8>(P, LG, rho, u, usq, theta, H, omega, dq, vg, dst, b, node, step);
 }
 
 // --------------------------------------------------------------------------
