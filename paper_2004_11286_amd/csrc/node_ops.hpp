@@ -1065,13 +1065,24 @@ struct SpeciesFlow<S, M, false> {
 // = d_x (e_y e_z) + (e - d)_x (d_y e_z + (e - d)_y d_z). The two (y, z) factors take
 // nine values each and K_c goes into the x factors: 81 operations per species c and
 // two per direction, where the direction-by-direction form takes about 160, and one
-// species' triplets at a time in registers.
-template <typename F, typename R, int M>
-__host__ __device__ __forceinline__ void species_source(const F (&u)[3], const F (&zeta)[M], const F (&V)[M][3],
+// species' triplets at a time in registers. FRESH: the triplets are formed again for each
+// lattice; they are the same for all, and the compiler keeps them (18 values per species c)
+// from the first lattice to the last. The three-pass collisions spilled for them (C_v(T), M = 4, the
+// split species collision: 65 registers in FP32, 221 in FP64; a step on 131 x 97 x 71 nodes 0.72 -> 0.56 and
+// 1.28 -> 0.96 ms). Not in the split collision of two species, which has registers left (weak
+// coupling with C_v(T), FP32: 1% slower), nor in the state passes (the whole register file, or few species).
+template <typename F, typename R, int M, bool FRESH>
+__host__ __device__ __forceinline__ void species_source(const F (&uin)[3], const F (&zeta)[M], const F (&V)[M][3],
                                                         const R (&Ka)[M], F (&out)[Q])
 {
 #pragma unroll
   for (int i = 0; i < Q; ++i) out[i] = F(0);
+  F u[3];
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    if constexpr (FRESH) u[k] = fresh(uin[k]);
+    else u[k] = uin[k];
+  }
 #pragma unroll
   for (int c = 0; c < M; ++c) {
     Trip<F> e[3], d[3];
@@ -1103,7 +1114,7 @@ __host__ __device__ __forceinline__ void species_source(const F (&u)[3], const F
 // the velocity the species see; F is evaluated in FP32 unless the storage is FP64
 // (a small correction); gD the factor (T_ref / T)^s_D of temperature-dependent
 // transport (1 otherwise).
-template <typename S, typename R, int M, int BC, bool CVT>
+template <typename S, typename R, int M, int BC, bool CVT, bool FRESH>
 __host__ __device__ __forceinline__ void species_relax(const Params<R>& P, const Mix<R, M>& s, const R (&K)[M][M],
                                                        const SpeciesFlow<S, M>& fl, const R (&us)[3], R gD,
                                                        int a, S (&v)[Q], S* __restrict__ dst, const Nbr& b,
@@ -1125,7 +1136,7 @@ __host__ __device__ __forceinline__ void species_relax(const Params<R>& P, const
   Rng rng(node, a, step);
   if constexpr (factored<S>()) {
     F32 F[Q];
-    species_source<F32, R, M>(fl.u, fl.zeta, fl.V, K[a], F);
+    species_source<F32, R, M, FRESH>(fl.u, fl.zeta, fl.V, K[a], F);
     const R b2 = R(2) * beta, b1 = R(1) - b2, bF = beta - R(1);
     const R px[3] = {s.rho_a[a] * pa[0].m, s.rho_a[a] * pa[0].z, s.rho_a[a] * pa[0].p};
 #pragma unroll
@@ -1491,7 +1502,7 @@ __host__ __device__ __forceinline__ void collide_node(const Params<R>& P, const 
     for (int a = 0; a < NS; ++a) {
       S v[Q];
       load(a, v);
-      species_relax<S, R, M, BC, CVT>(P, s, K, fl, us, gD, a, v, dst, b, node, step);
+      species_relax<S, R, M, BC, CVT, (PART == 0 ? NS >= 2 : M >= 3)>(P, s, K, fl, us, gD, a, v, dst, b, node, step);
       lattice_barrier();
     }
   }
@@ -1729,7 +1740,7 @@ __host__ __device__ __forceinline__ void state_species_node(const Params<R>& P, 
 #pragma unroll
       for (int i = 0; i < Q; ++i) va[i] = held[(a * Q + i) * HS];
     }
-    species_relax<S, R, M, BC, false>(P, s, K, fl, us, R(1), a, va, dst, b, node, step);
+    species_relax<S, R, M, BC, false, false>(P, s, K, fl, us, R(1), a, va, dst, b, node, step);
     lattice_barrier();
   }
 }

@@ -73,3 +73,8 @@ def _check(built, pattern, count, vgprs):
 def test_16_bit_state_passes_at_x_walls(built):
     """Three and four species, strong coupling, both occupancy variants: two waves per SIMD, nothing spilled."""
     _check(built, r"k_state_speciesI(DF16_f|DF16bf|sf)fLi[34]ELi1ELi[01]ELb0E", 12, 256)
+
+
+def test_split_species_collisions_of_the_property_step(built):
+    """Temperature-dependent properties, FP32 storage, three and four species, every boundary, both couplings."""
+    _check(built, r"k_collideIfdfLi[34]ELi[01245]ELi0ELi1ELb[01]ELb1E", 20, 256)
