@@ -189,16 +189,18 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(collide_p
 // fixed-point k_collide_fg on 190 x 164 x 156 nodes at two waves: 599 us without the
 // bound, 424 us with it). 16-bit state passes
 // keep their registers low by themselves (four waves) and are left free.
-// Three stored species or more in FP64 arithmetic, and two with FP64 storage too, take
-// one wave and the whole register file (four species at two waves spill 288 bytes per
-// lane).
+// With three species or more, three stored lattices or more in FP64 arithmetic, and two
+// with FP64 storage too, take one wave and the whole register file (four species at two
+// waves spill 288 bytes per lane). Variant 1 is the other number of waves that was worth
+// having: with two species three, but one where two lattices are stored in FP64 (weak
+// coupling, 131 x 97 x 71: 0.33 ms, at three waves, spilling 192 registers, 0.56 ms).
 template <typename S, typename R, int M, int V, bool WEAK>
 constexpr int state_waves()
 {
   constexpr int NS = Lat<M, WEAK>::NS;
   if (sizeof(S) == 2) return moment_waves<M, V>();
   const bool two = M == 2 || sizeof(R) == 4 || (NS == 2 && sizeof(S) == 4);
-  return V == 0 ? (two ? 2 : 1) : (M == 2 ? 3 : (two ? 1 : 2));
+  return V == 0 ? (two ? 2 : 1) : (M == 2 && !(NS == 2 && sizeof(S) == 8) ? 3 : (two ? 1 : 2));
 }
 template <typename S, typename R, int M, int V, bool WEAK>
 constexpr int state_waves_max() { return sizeof(S) == 2 ? 8 : state_waves<S, R, M, V, WEAK>(); }
@@ -222,21 +224,24 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(state_wav
 }
 
 // Occupancy targets of k_collide_fg: two waves per SIMD (variant 0; about 230
-// registers), or no bound on the registers (variant 1: one wave per SIMD).
+// registers). Variant 1 takes one wave in FP64 storage (weak coupling, 131 x 97 x 71: 0.217 and 0.205
+// ms), leaves fixed point unbounded, and is the same as variant 0 otherwise: held to one wave, FP32 takes
+// 0.124 against 0.105 ms, fixed point at x walls 0.131 against 0.093 ms and FP16 there 0.104 against 0.081 ms.
 // 16-bit floating point fits three waves by itself and is left free above (131 x 97 x
 // 89: 96 us, held to two waves 103 us), except at reflecting walls, whose selections
 // need two waves' registers (160 x 150 x 140 with x walls, BF16: 275 us, left free 442 us;
 // FP16 282 and 360 us).
-template <int V>
-constexpr int collide_fg_waves() { return V == 0 ? 2 : 1; }
+template <typename S, int V>
+constexpr int collide_fg_waves() { return V == 0 || !(sizeof(S) == 8 || is_fixed16<S>()) ? 2 : 1; }
 template <typename S, int W, int V>
 constexpr int collide_fg_waves_max()
 {
-  return sizeof(S) == 2 && !is_fixed16<S>() && !reflecting(W) ? 8 : collide_fg_waves<V>();
+  if (is_fixed16<S>()) return V == 0 ? 2 : 8;
+  return sizeof(S) == 2 && !reflecting(W) ? 8 : collide_fg_waves<S, V>();
 }
 
 template <typename S, typename R, typename Rec, int M, int W, int V, bool WEAK>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(collide_fg_waves<V>(), collide_fg_waves_max<S, W, V>()))) void k_collide_fg(
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(collide_fg_waves<S, V>(), collide_fg_waves_max<S, W, V>()))) void k_collide_fg(
     const Params<R>* __restrict__ P, Launch Ln, const S* __restrict__ src, S* __restrict__ dst,
     const Rec* __restrict__ rec, const Rec* __restrict__ G, StepNo sn)
 {

@@ -78,3 +78,8 @@ def test_16_bit_state_passes_at_x_walls(built):
 def test_split_species_collisions_of_the_property_step(built):
     """Temperature-dependent properties, FP32 storage, three and four species, every boundary, both couplings."""
     _check(built, r"k_collideIfdfLi[34]ELi[01245]ELi0ELi1ELb[01]ELb1E", 20, 256)
+
+
+def test_fp64_state_passes_of_two_weakly_coupled_species(built):
+    """Occupancy variant 1, every boundary: the whole register file of one wave per SIMD, nothing spilled."""
+    _check(built, r"k_state_speciesIdddLi2ELi[01245]ELi1ELb1E", 5, 512)
