@@ -5,6 +5,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "node_ops.hpp"
 
 namespace mclbm {
@@ -386,22 +388,32 @@ __global__ __launch_bounds__(BLOCK) void k_init(const Params<double>* __restrict
 // Fixed-point storage: the smallest and largest stored integer of every lattice
 // and direction class of every tube, into out[((t MAXL + l) NCLS + k) 2 + {0, 1}]
 // (the host sets the entries to 32767 and -32767 first). A launch over the
-// linear numbering: block b takes the RANGE_BLOCKS consecutive blocks from
-// b RANGE_BLOCKS, one lattice each (blockIdx.y), and keeps the running extremes of a
-// tube in registers until the tube changes; then one reduction over the workgroup
-// and one atomic per class and bound. The atomics all go to the same few words:
-// with one per wavefront, class and bound (3.6 million on 190 x 164 x 156 nodes) they
-// took 17.7 ms; with one per workgroup, and only where it widens the range seen so
-// far, the pass is bound by its reads (0.20 ms, 3.9 TB/s).
+// linear numbering: workgroup b takes `per` consecutive blocks from b per, one lattice
+// each (blockIdx.y), and keeps the running extremes of a tube in registers until the
+// tube changes; then one reduction over the workgroup and one atomic per class and
+// bound. The atomics all go to the same few words: with one per wavefront, class and
+// bound (3.6 million on 190 x 164 x 156 nodes) they took 17.7 ms; with one per
+// workgroup, and only where it widens the range seen so far, the pass is bound by its
+// reads (0.20 ms, 3.9 TB/s). A workgroup's blocks follow one another, each with its
+// loads' latency and, in a batch of small tubes, with a reduction of its own. So `per`
+// grows to RANGE_BLOCKS only as far as a workgroup per compute unit and lattice is left
+// (64 x 8 x 8 nodes: the initialisation, six of these passes, 0.51 ms at 16 throughout, 0.40 ms
+// so), and two per compute unit in a batch, whose tubes have words of their own (64 tubes
+// of 8..40 x 4 x 4: 1.84 and 1.40 ms; 512 tubes of 8..40 x 1 x 1: 4.96 and 4.43 ms; one tube of
+// 64^3 nodes 0.63 ms with one, 0.67 ms with two).
 constexpr int RANGE_BLOCKS = 16;
+inline int range_blocks(int nblocks, int ntubes)
+{
+  return std::max(1, std::min(RANGE_BLOCKS, nblocks / (ntubes > 1 ? 512 : 256)));
+}
 
 template <int M, bool WEAK>
-__global__ __launch_bounds__(BLOCK) void k_range16(const Params<double>* __restrict__ P, Launch Ln, int nblocks,
+__global__ __launch_bounds__(BLOCK) void k_range16(const Params<double>* __restrict__ P, Launch Ln, int nblocks, int per,
                                                    const int16_t* __restrict__ pop, int32_t* __restrict__ out)
 {
   __shared__ int red[BLOCK / 64][NCLS][2];
   const int l = blockIdx.y, wave = threadIdx.x >> 6;
-  const int b0 = (int)blockIdx.x * RANGE_BLOCKS, b1 = min(b0 + RANGE_BLOCKS, nblocks);
+  const int b0 = (int)blockIdx.x * per, b1 = min(b0 + per, nblocks);
   int lo[NCLS], hi[NCLS];
   auto reset = [&]() {
 #pragma unroll
@@ -617,8 +629,9 @@ Ops make_ops()
   o.rebase16 = nullptr;
   if constexpr (is_fixed16<S>()) {
     o.range16 = [](const void* Pd, const Launch& ln, const void* pop, int32_t* out, unsigned grid, hipStream_t st) {
-      hipLaunchKernelGGL((k_range16<M, WEAK>), dim3((grid + RANGE_BLOCKS - 1) / RANGE_BLOCKS, Lat<M, WEAK>::L), dim3(BLOCK),
-                         0, st, (const Params<double>*)Pd, ln, (int)grid, (const int16_t*)pop, out);
+      const int per = range_blocks((int)grid, ln.ntubes);
+      hipLaunchKernelGGL((k_range16<M, WEAK>), dim3((grid + per - 1) / per, Lat<M, WEAK>::L), dim3(BLOCK), 0, st,
+                         (const Params<double>*)Pd, ln, (int)grid, per, (const int16_t*)pop, out);
     };
     o.rebase16 = [](const void* Pd, const Launch& ln, void* pop, const double* tab, uint32_t seed, unsigned grid,
                     hipStream_t st) {

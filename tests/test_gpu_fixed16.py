@@ -177,3 +177,26 @@ def test_initial_ranges_see_the_last_node(mc, nx, ny, nz):
             assert np.abs(v[l][_CLS == k]).max() <= 16400, (l, k)
     ref = f["p"].reshape(-1)[-1]
     assert abs(p[-1] - ref) < 5e-4 * ref
+
+
+# blocks: 511 and 512 (one and two to a workgroup), 537 (two, a ragged last one), 4112 (sixteen, one left over)
+@pytest.mark.parametrize("nx,ny,nz", [(16, 16, 511), (16, 16, 512), (37, 53, 70), (64, 64, 257)])
+def test_initial_ranges_over_shared_workgroups(mc, nx, ny, nz):
+    """The range measurement gives a workgroup one block to sixteen, by the number of blocks: the extreme
+    pressure sits at the first node of the last block, and no stored value may pass half of its range."""
+    params, f = W.shear_layer(nx=nx, ny=ny, nz=nz)
+    n = nx * ny * nz
+    at = (n - 1) // 256 * 256
+    f["p"] = np.array(f["p"])
+    f["p"].reshape(-1)[at] *= 1.2
+    s = mc.Sim(params, mc.MCLBM_I16)
+    s.init_fields(**f)
+    _, vals = decode_checkpoint(s.save())
+    p = s.read_moments()["p"].reshape(-1)
+    s.close()
+    v = vals.reshape(vals.shape[0], 27, -1)
+    for l in range(v.shape[0]):
+        for k in range(8):
+            assert np.abs(v[l][_CLS == k].astype(np.int32)).max() <= 16400, (l, k)
+    ref = f["p"].reshape(-1)[at]
+    assert abs(p[at] - ref) < 5e-4 * ref
