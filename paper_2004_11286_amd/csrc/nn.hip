@@ -376,6 +376,10 @@ __global__ __launch_bounds__(256, (conv_waves<CIN, COUT, EPI, FLAT>())) void k_c
 // twice the time of the products (64 x 64, 590 k nodes of 4096 tubes: 65.5 -> 36 us).
 // The bias gradient is one more product, dY with a column of ones, in the wavefronts that
 // hold the first input channels of the (0, 0) column: a pass of its own over dY and its reduction took 32 us.
+// Each chunk's product starts from zero and the chunks are added with their rounding errors
+// carried along: in one FP32 accumulator over all of a workgroup's chunks (over a thousand
+// dependent additions on a million nodes of wide tubes) the error against 64 bits was two to
+// three times that of sums over 256 nodes and a tree.
 //
 // FLAT (every tube one node wide in y and z): the chunks run across the tubes as k_conv's tiles
 // do, and the y and z shifts wrap onto the node itself, so the nine (dy, dz) columns would
@@ -414,6 +418,15 @@ __global__ __launch_bounds__(256, 2) void k_wgrad(const NTube* __restrict__ tube
   for (int v = 0; v < 16; ++v) {
     acc[0][v] = acc[1][v] = acc[2][v] = accb[v] = 0.f;
   }
+  // bias: every column of a chunk's product holds the same sums, so lane l adds up row
+  // l & 15 of its half (the channel bco) and the rounding errors of that sum
+  float bsum = 0.f, berr = 0.f;
+  const int bv = lane & 15, bco = mb * 32 + 8 * (bv / 4) + 4 * (lane >> 5) + bv % 4;
+  auto bias_add = [&](float x) {                      // Knuth's two-sum
+    const float t = bsum + x, d = t - bsum;
+    berr += (bsum - (t - d)) + (x - d);
+    bsum = t;
+  };
   for (int e = threadIdx.x; e < SY; e += 256) ys[ZY * SY + e] = (bf16)0.f;
   for (int e = threadIdx.x; e < SX; e += 256) xs[ZX * SX + e] = (bf16)0.f;
 
@@ -513,6 +526,15 @@ __global__ __launch_bounds__(256, 2) void k_wgrad(const NTube* __restrict__ tube
           acc[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, join(b[d][0], b[d][1]), acc[d], 0, 0, 0);
         if (with_bias) accb = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, ones, accb, 0, 0, 0);
       }
+      if (with_bias) {
+        float x = accb[0];
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          if (v) x = bv == v ? accb[v] : x;
+          accb[v] = 0.f;
+        }
+        bias_add(x);
+      }
     }
   }
   if (wave >= NB) return;
@@ -523,8 +545,8 @@ __global__ __launch_bounds__(256, 2) void k_wgrad(const NTube* __restrict__ tube
 #pragma unroll
     for (int d = 0; d < 3; ++d)
       partial[(((size_t)g * (FLAT ? 3 : NTAP) + tap0 + d) * COUT + co) * CIN + ci] = acc[d][v];
-    if (with_bias && (lane & 31) == 0) bpart[(size_t)g * COUT + co] = accb[v];
   }
+  if (with_bias && (lane & 16) == 0) bpart[(size_t)g * COUT + bco] = __builtin_isfinite(bsum) ? bsum + berr : bsum;
 }
 
 // grad[tap][co][j] += sum_g partial[g][tap][co][col] over the parameters of a
@@ -535,11 +557,12 @@ __global__ __launch_bounds__(256, 2) void k_wgrad(const NTube* __restrict__ tube
 // y and z) the partials are [G][dx][COUTP][CINP]: each sum is formed once per dx
 // and added to the gradient of its nine taps.
 //
-// A workgroup takes 128 consecutive padded sums (the last one the bias gradient's), wave w
-// the w-th of eight slices of g, two sums a lane; the slices are then added in order. What
-// bounds it is how much of the 25 MB of partials lies side by side under one load: 32 sums
-// a slice, one load in flight after another, took 22 us on 504 groups of 3 x 64 x 64,
-// 10 us so.
+// A workgroup takes 128 consecutive padded sums, wave w the w-th of eight slices of g, two
+// sums a lane; the slices are then added in order. What bounds it is how much of the 25 MB
+// of partials lies side by side under one load: 32 sums a slice, one load in flight after
+// another, took 22 us on 504 groups of 3 x 64 x 64, 10 us so. The last workgroup adds the
+// bias gradient's partials, in FP64: 63 of them one after another in FP32 (504 groups in eight
+// slices) rounded more than the tree over the tiles' sums that they replaced.
 constexpr int WR_SLICES = 8, WR_OUT = 128;
 
 __global__ __launch_bounds__(64 * WR_SLICES) void k_wgrad_reduce(const float* __restrict__ partial,
@@ -550,11 +573,24 @@ __global__ __launch_bounds__(64 * WR_SLICES) void k_wgrad_reduce(const float* __
   __shared__ float2 red[WR_SLICES][WR_OUT / 2];
   __shared__ float total[WR_OUT];
   const int lane = threadIdx.x & 63, sl = threadIdx.x >> 6;
-  const bool bias = blockIdx.x == gridDim.x - 1;                // COUTP <= WR_OUT sums
-  const size_t gs = bias ? COUTP : (size_t)(flat ? 3 : NTAP) * COUTP * CINP;   // weights: a multiple of WR_OUT
-  const size_t e0 = bias ? 0 : (size_t)blockIdx.x * WR_OUT;
+  if (blockIdx.x == gridDim.x - 1) {           // the bias gradient
+    __shared__ double bred[WR_SLICES][64];
+    const int c = min((int)threadIdx.x & 63, COUTP - 1);
+    double s = 0.0;
+#pragma unroll 16
+    for (int g = (int)threadIdx.x >> 6; g < G; g += WR_SLICES) s += (double)bpart[(size_t)g * COUTP + c];
+    bred[threadIdx.x >> 6][threadIdx.x & 63] = s;
+    __syncthreads();
+    if ((int)threadIdx.x >= co_r) return;
+#pragma unroll
+    for (int q = 1; q < WR_SLICES; ++q) s += bred[q][c];
+    bgrad[c] += (float)s;
+    return;
+  }
+  const size_t gs = (size_t)(flat ? 3 : NTAP) * COUTP * CINP;   // a multiple of WR_OUT
+  const size_t e0 = (size_t)blockIdx.x * WR_OUT;
   const int g0 = (int)((int64_t)G * sl / WR_SLICES), g1 = (int)((int64_t)G * (sl + 1) / WR_SLICES);
-  const float* src = (bias ? bpart : partial) + e0 + min(2 * lane, (int)gs - 2);
+  const float* src = partial + e0 + 2 * lane;
   float2 s = {0.f, 0.f};
   constexpr int U = 16;                        // loads in flight; the additions in the order of g
   int g = g0;
@@ -584,10 +620,6 @@ __global__ __launch_bounds__(64 * WR_SLICES) void k_wgrad_reduce(const float* __
   }
   __syncthreads();
   if (k >= WR_OUT) return;
-  if (bias) {
-    if (k < co_r) bgrad[k] += total[k];
-    return;
-  }
   // rows of CINP sums: the block holds whole rows
   const size_t row = (e0 + k) / CINP;
   const int col = (int)((e0 + k) % CINP), co = (int)(row % COUTP), tap = (int)(row / COUTP);   // flat: tap = dx + 1
@@ -1288,7 +1320,7 @@ void wgrad(mclbm_nn* net, const bf16* dY, const bf16* X, int layer)
   // only the real channels have parameters (the padded ones stay zero)
   const int co_r = net->out_r[layer], ci_r = net->in_r[layer];
   const int n = (flat ? 3 : NTAP) * COUT * CIN;
-  static_assert(WR_OUT % CIN == 0 && COUT * CIN % WR_OUT == 0 && COUT <= WR_OUT, "whole rows per workgroup");
+  static_assert(WR_OUT % CIN == 0 && COUT * CIN % WR_OUT == 0 && COUT <= 64, "whole rows per workgroup");
   hipLaunchKernelGGL(k_wgrad_reduce, dim3(n / WR_OUT + 1), dim3(64 * WR_SLICES), 0, net->stream, net->wpart,
                      net->bpart, G, COUT, CIN, co_r, ci_r, layer == 0 ? net->C : ci_r, layer == 0 ? net->P : 0,
                      net->grad + net->w_off[layer], net->grad + net->b_off[layer], flat ? 1 : 0);

@@ -620,3 +620,42 @@ def test_network_arguments_are_checked(env):
     net.close()
     with pytest.raises(mc.MclbmError):
         mc.Net(7, 3, DIMS, species=3)                                 # conservative form needs M + 5 channels
+
+
+@pytest.mark.parametrize("dims,period", [([(128, 32, 32)] * 8, 8192), ([(128, 1, 1)] * 4096, 504)])
+def test_bias_gradient_keeps_its_digits_over_long_sums(env, dims, period):
+    """The last layer's bias gradient is -2/n times the sum of the target (zero parameters, inputs and
+    shifts; n a power of two and a BF16 target, so every term is exact). The target's size is spread over
+    nine powers of two (mean 1/3), so that its sums need more bits than FP32 has. It is positive on the
+    first half of every period of 128-node chunks and negative on the second, which lets the partial sums
+    grow (within a workgroup on wide tubes, 56 of which take every 56th chunk; over the slices of the
+    reduction on one-node-wide ones, whose 504 take every 504th) and the total nearly vanish.
+
+    Bound: a chunk's 128 nodes are eight FP32 accumulations below 128, each within 2^-18; over the n / 16
+    accumulations of a channel, uniformly distributed and independent, that is sqrt(n / 16) 2^-18 / sqrt(3)
+    (5.6e-4 and 4.0e-4), times 2 / n at most 1.5e-9: 8e-9 is five of these. One FP32 sum over a workgroup's
+    chunks (to 3e3, 1170 additions) and over a slice (to 2e4, 63 additions) would give 2e-8 and more."""
+    mc, torch = env
+    n = sum(a * b * c for a, b, c in dims)
+    rng = np.random.default_rng(5)
+    sign = np.where((np.arange(n) // 128) % period < period // 2, 1.0, -1.0)
+    size = rng.uniform(1.0, 2.0, (C, n)) * 2.0 ** rng.integers(-8, 1, (C, n))
+    t = torch.tensor(sign * size, dtype=torch.float32).to(torch.bfloat16).to(torch.float32)
+    want = -2.0 / n * t.double().sum(dim=1).numpy()
+    # channel-major within each tube
+    parts, at = [], 0
+    for a, b, c in dims:
+        parts.append(t[:, at:at + a * b * c].reshape(-1))
+        at += a * b * c
+    net = mc.Net(C, 2, dims)
+    net.set_params(np.zeros(net.param_count, np.float32))
+    net.set_norm(np.zeros(C, np.float32), np.ones(C, np.float32), np.ones(C, np.float32))
+    net.forward(torch.zeros(C * n, device="cuda"))
+    net.loss(torch.cat(parts).cuda())
+    net.zero_grad()
+    net.backward()
+    got = net.get_grads()[-C:].astype(np.float64)
+    net.close()
+    err = float(np.abs(got - want).max())
+    print("bias gradient", dims[0], "error", err, "largest", float(np.abs(want).max()))
+    assert err < 8e-9
