@@ -374,6 +374,10 @@ __global__ __launch_bounds__(256, (conv_waves<CIN, COUT, EPI, FLAT>())) void k_c
 // loaded into registers while the current chunk's products run. Staged transposed
 // instead, with one 2-byte store per value and a copy of X per tap, the LDS stores took
 // twice the time of the products (64 x 64, 590 k nodes of 4096 tubes: 65.5 -> 36 us).
+// Where a layer has two 32 x 32 blocks (the first and the last one) two wavefronts share a
+// block, taking its 16-node steps in turn: a chunk costs a wavefront its chain of LDS reads and
+// products whatever the others do, and with half of the wavefronts idle these layers took as
+// long as the full ones (8 tubes of 128 x 32 x 32: 504 and 491 us, shared 369 and 364 us).
 // The bias gradient is one more product, dY with a column of ones, in the wavefronts that
 // hold the first input channels of the (0, 0) column: a pass of its own over dY and its reduction took 32 us.
 // Each chunk's product starts from zero and the chunks are added with their rounding errors
@@ -404,15 +408,18 @@ __global__ __launch_bounds__(256, 2) void k_wgrad(const NTube* __restrict__ tube
   constexpr int SY = COUT + 8, SX = CIN + 8;          // LDS row strides: the 16 lanes of a read cover 32 banks once
   constexpr int ZY = WCH, ZX = WCH + 2;               // rows of zeros
   constexpr int NB = (COUT / 32) * (CIN / 32);
-  static_assert(NB <= 4, "one 32 x 32 block per wavefront");
-  __shared__ __attribute__((aligned(16))) bf16 ys[(WCH + 1) * SY];
-  __shared__ __attribute__((aligned(16))) bf16 xs[(WCH + 3) * SX];
+  static_assert(NB == 2 || NB == 4, "one 32 x 32 block per wavefront, or per two");
+  constexpr int PARTS = 4 / NB;                       // wavefronts that share a block
+  constexpr int YLEN = (WCH + 1) * SY, XLEN = (WCH + 3) * SX;
+  __shared__ __attribute__((aligned(16))) bf16 lds[YLEN + XLEN];
+  bf16 *ys = lds, *xs = lds + YLEN;
+  static_assert(YLEN % 8 == 0, "rows of X aligned to 16 bytes");
   const int yz = FLAT ? 4 : (int)blockIdx.y, g = blockIdx.x, G = gridDim.x;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int dy = yz % 3 - 1, dz = yz / 3 - 1;
   const int tap0 = FLAT ? 0 : 9 * (dz + 1) + 3 * (dy + 1);   // taps tap0 + k, dx = k - 1
-  const int mb = wave / (CIN / 32), cb = wave % (CIN / 32);
-  const bool with_bias = wave < NB && cb == 0 && yz == 4;
+  const int part = wave / NB, mb = wave % NB / (CIN / 32), cb = wave % (CIN / 32);
+  const bool with_bias = cb == 0 && yz == 4;
   f32x16 acc[3], accb;
 #pragma unroll
   for (int v = 0; v < 16; ++v) {
@@ -501,43 +508,68 @@ __global__ __launch_bounds__(256, 2) void k_wgrad(const NTube* __restrict__ tube
     __syncthreads();
     load_rows(min(ch + G, nchunks - 1));
     __builtin_amdgcn_sched_barrier(0);
-    if (wave < NB) {
-      for (int k0 = 0; k0 < count; k0 += 16) {
-        const uint32_t los = (uint32_t)(lo[k0 >> 6] >> (k0 & 63)), his = (uint32_t)(hi[k0 >> 6] >> (k0 & 63));
-        i16x4 a[2], b[3][2];
+    for (int k0 = 16 * part; k0 < count; k0 += 16 * PARTS) {
+      const uint32_t los = (uint32_t)(lo[k0 >> 6] >> (k0 & 63)), his = (uint32_t)(hi[k0 >> 6] >> (k0 & 63));
+      i16x4 a[2], b[3][2];
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          const int k = k0 + kl + 4 * h;
-          const bool in = k < count;
-          const bool first = (los >> (kl + 4 * h)) & 1, last = (his >> (kl + 4 * h)) & 1;
-          a[h] = lds_read_tr(&ys[(in ? k : ZY) * SY + mb * 32 + colb]);
+      for (int h = 0; h < 2; ++h) {
+        const int k = k0 + kl + 4 * h;
+        const bool in = k < count;
+        const bool first = (los >> (kl + 4 * h)) & 1, last = (his >> (kl + 4 * h)) & 1;
+        a[h] = lds_read_tr(&ys[(in ? k : ZY) * SY + mb * 32 + colb]);
 #pragma unroll
-          for (int d = 0; d < 3; ++d) {
-            const int r = in ? k + 1 + (d == 0 ? (first ? 0 : -1) : (d == 2 ? (last ? 0 : 1) : 0)) : ZX;
-            b[d][h] = lds_read_tr(&xs[r * SX + cb * 32 + colb]);
-          }
+        for (int d = 0; d < 3; ++d) {
+          const int r = in ? k + 1 + (d == 0 ? (first ? 0 : -1) : (d == 2 ? (last ? 0 : 1) : 0)) : ZX;
+          b[d][h] = lds_read_tr(&xs[r * SX + cb * 32 + colb]);
         }
-        auto join = [](i16x4 p, i16x4 q) {
-          return __builtin_bit_cast(bf16x8, __builtin_shufflevector(p, q, 0, 1, 2, 3, 4, 5, 6, 7));
-        };
-        const bf16x8 av = join(a[0], a[1]);
-#pragma unroll
-        for (int d = 0; d < 3; ++d)
-          acc[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, join(b[d][0], b[d][1]), acc[d], 0, 0, 0);
-        if (with_bias) accb = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, ones, accb, 0, 0, 0);
       }
-      if (with_bias) {
-        float x = accb[0];
+      auto join = [](i16x4 p, i16x4 q) {
+        return __builtin_bit_cast(bf16x8, __builtin_shufflevector(p, q, 0, 1, 2, 3, 4, 5, 6, 7));
+      };
+      const bf16x8 av = join(a[0], a[1]);
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          if (v) x = bv == v ? accb[v] : x;
-          accb[v] = 0.f;
-        }
-        bias_add(x);
+      for (int d = 0; d < 3; ++d)
+        acc[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, join(b[d][0], b[d][1]), acc[d], 0, 0, 0);
+      if (with_bias) accb = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, ones, accb, 0, 0, 0);
+    }
+    if (with_bias) {
+      float x = accb[0];
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        if (v) x = bv == v ? accb[v] : x;
+        accb[v] = 0.f;
       }
+      bias_add(x);
     }
   }
-  if (wave >= NB) return;
+  if constexpr (PARTS == 2) {                         // add the second wavefront's sums of a block
+    __shared__ float bias2[COUT][2];
+    static_assert((YLEN + XLEN) * 2 >= NB * 48 * 64 * 4, "the sums of two wavefronts fit the rows' LDS");
+    float* sums = (float*)lds + (wave % NB) * 48 * 64;
+    __syncthreads();                                  // the last chunk's reads
+    if (part == 1) {
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+#pragma unroll
+        for (int d = 0; d < 3; ++d) sums[(16 * d + v) * 64 + lane] = acc[d][v];
+      }
+      if (with_bias && (lane & 16) == 0) {
+        bias2[bco][0] = bsum;
+        bias2[bco][1] = berr;
+      }
+    }
+    __syncthreads();
+    if (part == 1) return;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+#pragma unroll
+      for (int d = 0; d < 3; ++d) acc[d][v] += sums[(16 * d + v) * 64 + lane];
+    }
+    if (with_bias) {
+      bias_add(bias2[bco][0]);
+      berr += bias2[bco][1];
+    }
+  }
 #pragma unroll
   for (int v = 0; v < 16; ++v) {
     const int co = mb * 32 + 8 * (v / 4) + 4 * (lane >> 5) + (v % 4);
