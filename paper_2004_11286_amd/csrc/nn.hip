@@ -132,6 +132,12 @@ __device__ inline int64_t wrap_index(const NTube& tb, int x, int y, int z)
 // terms once instead of nine times: 64 -> 64 adjoint 129 -> 104 us).
 // Together, the eleven conv launches of a training iteration: 1.95 -> 0.96 ms.
 // Every node's products and their order are the same as without FLAT.
+//
+// MIXED (some tubes one node wide in y and z among wider ones): a tile of such a tube keeps the rows
+// that it staged for the first group. With them staged again for each group the passes over 2048
+// such tubes and one of 128 x 8 x 8 took 0.58 and 2.17 ms instead of 0.51 and 2.00 ms;
+// the branch itself costs wide tubes 2% (8 x 128 x 32 x 32: 1.14 -> 1.165 ms), so networks
+// without such tubes are compiled without it.
 template <int CIN>
 __device__ __forceinline__ int lds_at(int row, int c) { return row * (CIN + 8) + (c << 3); }
 
@@ -141,7 +147,7 @@ constexpr int conv_waves()
   return COUT == 64 && (CIN == 64 || (EPI == 2 && !FLAT)) ? 2 : 3;   // what fits without spilling
 }
 
-template <int CIN, int COUT, int EPI, bool FLAT>
+template <int CIN, int COUT, int EPI, bool FLAT, bool MIXED>
 __global__ __launch_bounds__(256, (conv_waves<CIN, COUT, EPI, FLAT>())) void k_conv(const NTube* __restrict__ tubes, const int32_t* __restrict__ tile_tube,
                                                  int ntubes, const uint8_t* __restrict__ ends,
                                                  const bf16* __restrict__ W, const float* __restrict__ bias,
@@ -311,15 +317,16 @@ __global__ __launch_bounds__(256, (conv_waves<CIN, COUT, EPI, FLAT>())) void k_c
       at_walls(s, held[s]);
     }
   }
+  const bool restage = !FLAT && (!MIXED || tb.ny > 1 || tb.nz > 1);
 #pragma unroll 1
   for (int g = 0; g < 8; ++g) {
-    if constexpr (!FLAT) sload(g + 1);
+    if (restage) sload(g + 1);
 #pragma unroll
     for (int d = 0; d < 3; ++d) load_w(3 * g + 3 + d, d);
     __builtin_amdgcn_sched_barrier(0);
     group();
     __syncthreads();
-    if constexpr (!FLAT) sstore();
+    if (restage) sstore();
 #pragma unroll
     for (int d = 0; d < 3; ++d) store_w(d);
     __syncthreads();
@@ -1130,7 +1137,7 @@ struct mclbm_nn {
   int Ms = 0;                           // species of the conservative output (0: direct output)
   int Cout = 0;                         // output channels: C, or 3 Ms + 4
   int64_t n = 0, ntiles = 0;
-  bool flat_yz = false;                 // every tube is one node wide in y and z
+  bool mixed = false;                   // some tubes are one node wide in y and z, others not (or too many nodes for ends)
   hipStream_t stream = nullptr;
   std::string err;
   std::vector<NTube> hTubes;
@@ -1326,10 +1333,13 @@ void conv(mclbm_nn* net, const bf16* W, const float* b, const bf16* in, const bf
   // one row of all nodes where every tube is one node wide in y and z and the row's
   // indices fit the kernel's 32 bits
   if (net->ends)
-    hipLaunchKernelGGL((k_conv<CIN, COUT, EPI, true>), dim3(blocks_for(net->n, TILE)), dim3(256), 0, net->stream,
+    hipLaunchKernelGGL((k_conv<CIN, COUT, EPI, true, false>), dim3(blocks_for(net->n, TILE)), dim3(256), 0, net->stream,
                        net->dTubes, net->dTileTube, net->ntubes, net->ends, W, b, in, mask, out);
+  else if (net->mixed)
+    hipLaunchKernelGGL((k_conv<CIN, COUT, EPI, false, true>), dim3((unsigned)net->ntiles), dim3(256), 0, net->stream,
+                       net->dTubes, net->dTileTube, net->ntubes, nullptr, W, b, in, mask, out);
   else
-    hipLaunchKernelGGL((k_conv<CIN, COUT, EPI, false>), dim3((unsigned)net->ntiles), dim3(256), 0, net->stream,
+    hipLaunchKernelGGL((k_conv<CIN, COUT, EPI, false, false>), dim3((unsigned)net->ntiles), dim3(256), 0, net->stream,
                        net->dTubes, net->dTileTube, net->ntubes, nullptr, W, b, in, mask, out);
 }
 
@@ -1465,8 +1475,7 @@ extern "C" int mclbm_nn_create(int32_t channels, int32_t two_term, int32_t condi
     tile += tb.ntiles;
     base += n;
   }
-  net->flat_yz = true;
-  for (const NTube& tb : net->hTubes) net->flat_yz = net->flat_yz && tb.ny == 1 && tb.nz == 1;
+  for (const NTube& tb : net->hTubes) net->mixed = net->mixed || (!lay.flat && tb.ny == 1 && tb.nz == 1);
   if (lay.flat) {
     net->ends = (uint8_t*)(ws + lay.ends);
     net->hEnds.assign((size_t)lay.n, 0);

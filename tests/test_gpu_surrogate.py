@@ -659,3 +659,23 @@ def test_bias_gradient_keeps_its_digits_over_long_sums(env, dims, period):
     err = float(np.abs(got - want).max())
     print("bias gradient", dims[0], "error", err, "largest", float(np.abs(want).max()))
     assert err < 8e-9
+
+
+def test_mixed_networks_forward_each_tube_as_alone(env):
+    """A network of tubes one node wide in y and z among wider ones gives every tube, bit for bit,
+    what a network of that tube alone gives it (three compiled forms of the convolution: tubes of one
+    node's width only, none of them, and both); lengths at the edges of a 256-node tile."""
+    dims = [(255, 1, 1), (1, 1, 1), (13, 7, 5), (300, 1, 1), (31, 1, 5), (256, 1, 1), (257, 3, 1), (2, 1, 1)]
+    depth = 3
+    p = S.he_init(C, depth, seed=23, gain=1.0)
+    p += np.random.default_rng(24).normal(0, 0.02, p.size).astype(np.float32)
+    nm = norm_arrays(2)
+    fs = random_fields(25, dims=dims)
+    net = make_net(env, depth, p, nm, dims=dims)
+    got = split(net.forward(flat(env, fs)).cpu().numpy(), dims=dims)
+    net.close()
+    for t, d in enumerate(dims):
+        one = make_net(env, depth, p, nm, dims=[d])
+        want = one.forward(flat(env, [fs[t]])).cpu().numpy()
+        one.close()
+        np.testing.assert_array_equal(got[t].ravel(), want, err_msg=str(d))
