@@ -1070,7 +1070,9 @@ struct SpeciesFlow<S, M, false> {
 // from the first lattice to the last. The three-pass collisions spilled for them (C_v(T), M = 4, the
 // split species collision: 65 registers in FP32, 221 in FP64; a step on 131 x 97 x 71 nodes 0.72 -> 0.56 and
 // 1.28 -> 0.96 ms). Not in the split collision of two species, which has registers left (weak
-// coupling with C_v(T), FP32: 1% slower), nor in the state passes (the whole register file, or few species).
+// coupling with C_v(T), FP32: 1% slower), nor in the state passes (the whole register file, or few species),
+// nor at the jets: their two-read kernels, the same machine code, run 1% slower (200 x 400, 50 steps: 3.22 and
+// 3.25 ms) at the places in the code object that shorter three-pass kernels before them give them.
 template <typename F, typename R, int M, bool FRESH>
 __host__ __device__ __forceinline__ void species_source(const F (&uin)[3], const F (&zeta)[M], const F (&V)[M][3],
                                                         const R (&Ka)[M], F (&out)[Q])
@@ -1502,7 +1504,7 @@ __host__ __device__ __forceinline__ void collide_node(const Params<R>& P, const 
     for (int a = 0; a < NS; ++a) {
       S v[Q];
       load(a, v);
-      species_relax<S, R, M, BC, CVT, (PART == 0 ? NS >= 2 : M >= 3)>(P, s, K, fl, us, gD, a, v, dst, b, node, step);
+      species_relax<S, R, M, BC, CVT, xbc(BC) != BC_JETS && (PART == 0 ? NS >= 2 : M >= 3)>(P, s, K, fl, us, gD, a, v, dst, b, node, step);
       lattice_barrier();
     }
   }
