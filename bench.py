@@ -7,8 +7,9 @@ field, collide-and-stream over all 16.8 M nodes.
 
 Prints one JSON line (the last line of stdout) with MLUPS, the HBM roofline of
 the dominant kernel (timed with HIP events on the library's stream), the other
-storage precisions measured side by side with their per-field error against the
-FP32 run, and the FP64 CPU oracle timed on a bounded crop of the same workload.
+storage precisions measured side by side with their error against the FP32 run,
+and the FP64 CPU oracle timed on a bounded crop of the same workload. The whole
+record, of which the line holds the main figures, goes to stderr.
 
   python bench.py [--gpus 1] [--steps K] [--warmup W] [--precision fp32|fp32_fp32|fp16|bf16|i16|fp64]
 """
@@ -342,6 +343,51 @@ def finite_or_null(x):
     if isinstance(x, (list, tuple)):
         return [finite_or_null(v) for v in x]
     return x
+
+
+LINE_LIMIT = 4000            # bytes of the JSON line on stdout
+
+
+def line_of(record):
+    """The JSON line for stdout: the record with every float at six digits, each section cut to its
+    figures. The whole record is over 20 KB and goes to stderr; a reader that keeps only the
+    end of stdout must still see the line from its first byte."""
+    def pick(d, *keys):
+        return None if d is None else {k: d[k] for k in keys if k in d}
+
+    def six(x):
+        if isinstance(x, float):
+            return float(f"{x:.6g}")
+        if isinstance(x, dict):
+            return {k: six(v) for k, v in x.items()}
+        return [six(v) for v in x] if isinstance(x, list) else x
+
+    sections = ("timing", "config", "roofline", "kernels", "block_shapes", "step_effective_GBs", "variants",
+                "weak_coupling", "weak_fp16", "weak_i16", "cv_of_T", "weak_cv_of_T", "open_x", "ensemble", "surrogate",
+                "cpu_baseline")
+    line = {k: v for k, v in record.items() if k not in sections}
+    line["config"] = record["config"]
+    line["timing"] = pick(record["timing"], "method", "timed_region_s")
+    line["roofline"] = pick(record["roofline"], "bound", "kernel", "achieved", "peak", "unit", "frac", "frac_of_best_copy")
+    line["kernels_avg_ms"] = {k: v["avg_ms"] for k, v in record["kernels"].items()}
+
+    def short(d):
+        return None if d is None else {k: v for k, v in d.items() if k.startswith("speedup_vs_")
+                                       or k in ("MLUPS", "worst_field_error", "meets_1e-3")}
+
+    for k in ("weak_coupling", "weak_fp16", "weak_i16", "cv_of_T", "weak_cv_of_T", "open_x"):
+        line[k] = short(record[k])
+    line["variants"] = {k: short(v) for k, v in record["variants"].items()}
+    e, g = record["ensemble"], record["surrogate"]
+    line["ensemble"] = None if e is None else {"MLUPS": e["autotuned"]["MLUPS"], **pick(e, "speedup_batched_vs_sequential", "finite")}
+    line["surrogate"] = None if g is None else {
+        **pick(g, "workload", "train_tubes_left_out", "speedup_forward_vs_lattice"),
+        "train": pick(g["train"], "iters", "ms_per_step", "TFLOPs_per_step_approx", "loss_last100"),
+        "change_tol": g["gate_calibration"]["change_tol"],
+        "hops": [pick(r, "t0", "X_linf", "accepted", "ms_advance") for r in g["eval"]],
+        "conv_forward_TFLOPs": g["roofline_conv_forward"]["achieved"]}
+    line["cpu_baseline"] = pick(record["cpu_baseline"], "value", "unit", "cores")
+    return six(line)
 
 
 BF16_PEAK_TFLOPS = 2500.0   # MI355X dense BF16 matrix-core peak
@@ -688,7 +734,9 @@ def main():
         "surrogate": surrogate,
         "cpu_baseline": cpu,
     }
-    print(json.dumps(finite_or_null(out)))
+    record = finite_or_null(out)
+    print("full record: " + json.dumps(record), file=sys.stderr, flush=True)
+    print(json.dumps(line_of(record)))
 
 
 if __name__ == "__main__":
