@@ -10,7 +10,8 @@
 // by the four waves of a workgroup; the neighbour activations are the B operand,
 // staged in LDS per group of three taps; the accumulator holds 4 consecutive
 // output channels of one node per lane group, so results leave as 8- or 16-byte
-// vector stores. A workgroup computes 256 nodes of one tube (64 per wave, two
+// vector stores. A workgroup computes 256 nodes (of one tube, or of consecutive tubes
+// where every tube is one node wide in y and z; 64 per wave, two
 // 32-node column blocks) for all output channels.
 #include <hip/hip_runtime.h>
 
@@ -118,8 +119,8 @@ __device__ inline int64_t wrap_index(const NTube& tb, int x, int y, int z)
 // The loads stand under no branch, and a step's operands are read from LDS two steps
 // ahead of its MFMAs: with a load under a branch the wave waits for it where the
 // branch ends, and the kernel spent as long in those waits as in its products (the
-// 64 -> 64 forward on 1.05 M nodes: 229 -> 200 us, 1.16 PFLOP/s, the rate a large library
-// product reaches; halving the barriers alone: 236 us). Two workgroups fit in a compute
+// 64 -> 64 forward on 1.05 M nodes: 229 -> 200 us at best; 209 us or 1.11 PFLOP/s as the
+// median of a training run's evaluations; halving the barriers alone: 236 us). Two workgroups fit in a compute
 // unit: 64.8 KB of LDS each, rows padded by 16 bytes so that the 16 rows a quarter of a
 // wavefront reads at one piece cover the 64 banks once.
 //
@@ -1163,13 +1164,14 @@ struct mclbm_nn {
   bf16* dyl = nullptr;                  // gradient of the last layer's output [n][COUTL]
   float* wpart = nullptr;               // weight-gradient partials
   int wG = 0;                           // workgroups along the chunks (nine (dy, dz) columns each)
-  int wGf = 0;                          // the same with one column (flat_yz): up to nine times wG
+  int wGf = 0;                          // the same with one column (where ends is set): up to nine times wG
   float* bpart = nullptr;               // bias-gradient partials [wG or wGf][WIDTH]
   double* dpart = nullptr;              // loss / residual partials
   float* cond = nullptr;                // [ntubes][S] conditioning values
   float* fin = nullptr;                 // [C][n] input fields
   float* fout = nullptr;                // [C][n] predicted fields
-  uint8_t* ends = nullptr;              // [n] first / last node of its tube (bits 0, 1): flat_yz tubes
+  // [n] first / last node of its tube (bits 0, 1); set where every tube is one node wide in y and z
+  uint8_t* ends = nullptr;
   std::vector<uint8_t> hEnds;
 };
 
@@ -1262,7 +1264,8 @@ NNLayout nn_layout(int C, int P, int S, int Ms, int depth, const int32_t* dims, 
     bpb += align_up(sizeof(float) * out_p[k]);
   }
   // weight-gradient groups: 56 x 9 (dy, dz) workgroups fill the 256 compute units
-  // two deep (the 64 -> 64 kernel stages 68 KB of LDS: two workgroups per unit)
+  // nearly two deep; the partials, 25 MB a layer, grow with their number (three
+  // workgroups would fit a unit's registers, four its LDS)
   l.wG = (int)std::min<int64_t>(2 * l.ntiles, 56);
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o = off; off += align_up(bytes); return o; };

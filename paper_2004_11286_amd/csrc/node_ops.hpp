@@ -799,7 +799,7 @@ __host__ __device__ __forceinline__ void range_check(const Params<R>& P, const R
 // store per direction. Through the directions' own resources the reflected lanes needed
 // a branch and a second, global store in each of the 18 directions that cross a wall;
 // in the tubes nearly every wavefront holds a wall node (512 tubes of 32..256 x 16 x 16,
-// M = 3, FP32: k_collide_fg 5.31 -> 2.01 ms). The offsets need Q n values below 2^32
+// M = 3, FP32: k_collide_fg 5.31 -> 1.94 ms). The offsets need Q n values below 2^32
 // bytes; larger tubes store through 64-bit addresses.
 //
 // FRESH: the offsets are computed again for each lattice. They are the same for all lattices of
@@ -1581,10 +1581,11 @@ enum {
 };
 
 // Where state_species_node keeps the species populations between the moments and the
-// collision. One stored species, and three or more in FP64 arithmetic (whose kernel
-// has the whole register file at one wave per SIMD): registers, every load of the
-// node issued at the start. Two with 4-byte storage: LDS, 55 KB per workgroup, two
-// workgroups per compute unit. The rest read them a second time: eight waves' values
+// collision. One stored species, and three or more with FP32 storage and FP64 arithmetic
+// (whose kernel has the whole register file at one wave per SIMD): registers, every load
+// of the node issued at the start. Two with 4-byte storage: LDS, 55 KB per workgroup, two
+// workgroups per compute unit. The rest (two or more in FP64 or 16-bit storage, three or
+// more in FP32 arithmetic) read them a second time: eight waves' values
 // of all lattices do not stay in an XCD's 4 MB of L2, so the second read costs
 // nearly a first one (512 ternary tubes: 2.73 ms, read twice 3.39 ms; weak coupling,
 // 1.5 M nodes: 208 us, read twice 234 us; jets 200 x 400, M = 4: 36 us against 41 us).
@@ -1762,7 +1763,7 @@ __host__ __device__ __forceinline__ void fg_collide_node(const Params<R>& P, con
   // memory with two waves per SIMD, and loads after the moments cost it a second
   // latency (shear layer 256^3: 1.76 -> 1.63 ms). The walls' store offsets leave no
   // registers for it (512 ternary tubes: 2.64 ms so, 2.19 ms with the stencil loaded
-  // after the moments), nor does FP64 storage (64 x 8 x 8: 9.7 -> 12.3 us); the
+  // after the moments, both before the runs of blocks per XCD), nor does FP64 storage (64 x 8 x 8: 9.7 -> 12.3 us); the
   // 16-bit kernels are bound by instructions (190 x 164 x 156 fixed point: 466 -> 500
   // us).
   constexpr bool EARLY = sizeof(S) == 4 && !reflecting(BC);
