@@ -119,7 +119,7 @@ __device__ inline int64_t wrap_index(const NTube& tb, int x, int y, int z)
 // The loads stand under no branch, and a step's operands are read from LDS two steps
 // ahead of its MFMAs: with a load under a branch the wave waits for it where the
 // branch ends, and the kernel spent as long in those waits as in its products (the
-// 64 -> 64 forward on 1.05 M nodes: 229 -> 200 us at best; 209 us or 1.11 PFLOP/s as the
+// 64 -> 64 forward on 1.05 M nodes: 229 -> 197 us at best; 203 us or 1.14 PFLOP/s as the
 // median of a training run's evaluations; halving the barriers alone: 236 us). Two workgroups fit in a compute
 // unit: 64.8 KB of LDS each, rows padded by 16 bytes so that the 16 rows a quarter of a
 // wavefront reads at one piece cover the 64 banks once.
