@@ -50,19 +50,26 @@ def record_fields(M: int, weak: bool = False, cvt: bool = False) -> int:
 
 
 def algorithmic_bytes(M: int, s_bytes: int, r_bytes: int, weak: bool = False, cvt: bool = False) -> dict:
-    """Bytes each kernel must move per node, every value read or written once:
-    k_moments reads the populations and writes the record; k_gfield reads Phi and
-    omega and writes G; k_collide reads the populations, the record except Phi,
-    and G, and writes the populations. Stored lattices: M + 1 (strong coupling),
-    M + 2 (weak)."""
+    """Bytes each kernel must move per node, every value read or written once.
+    Two-read step: k_state_species reads the populations, writes the species' and
+    a record of 10 fields; k_gfield reads Phi and omega and writes G; k_collide_fg
+    reads the momentum and energy lattices, the record except Phi, a neighbour's
+    C_p and G, and writes both lattices. Three-pass step: k_moments reads the
+    populations and writes the record; k_collide reads the populations, the record
+    except Phi, and G, and writes the populations. `step` is the two-read step.
+    Stored lattices: M + 1 (strong coupling), M + 2 (weak)."""
     L = M + 2 if weak else M + 1
     pops = L * 27 * s_bytes
+    fg = 2 * 27 * s_bytes
     rec = record_fields(M, weak, cvt) * r_bytes
+    state, gfield, collide_fg = 2 * pops - fg + 10 * r_bytes, 7 * r_bytes, 2 * fg + 11 * r_bytes
     return {
+        "k_state_species": state,
+        "k_collide_fg": collide_fg,
         "k_moments": pops + rec,
-        "k_gfield": 4 * r_bytes + 3 * r_bytes,
+        "k_gfield": gfield,
         "k_collide": 2 * pops + (rec - 3 * r_bytes) + 3 * r_bytes,
-        "step": 3 * pops + 2 * rec + 7 * r_bytes,
+        "step": state + gfield + collide_fg,
         "method_min": 2 * pops,
     }
 

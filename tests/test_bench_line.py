@@ -64,3 +64,14 @@ def test_the_line_is_short_and_complete():
         if full:
             assert len(json.dumps(rec)) > 2 * bench.LINE_LIMIT
             assert line["variants"]["i16"]["MLUPS"] and len(line["surrogate"]["hops"]) == 6
+
+
+def test_two_read_step_bytes():
+    """Binary FP32 step: three lattices of 108 bytes read by the state pass and two again by the collision,
+    each written once; ten record fields written, seven read again; G and C_p of a neighbour, Phi and omega once."""
+    ab = bench.algorithmic_bytes(2, 4, 4)
+    assert ab["k_state_species"] == 3 * 108 + 108 + 40
+    assert ab["k_gfield"] == 16 + 12
+    assert ab["k_collide_fg"] == 216 + 28 + 16 + 216
+    assert ab["step"] == ab["k_state_species"] + ab["k_gfield"] + ab["k_collide_fg"] == 976
+    assert ab["method_min"] == 2 * 3 * 108
