@@ -375,7 +375,7 @@ def line_of(record):
     line = {k: v for k, v in record.items() if k not in sections}
     line["config"] = record["config"]
     line["timing"] = pick(record["timing"], "method", "timed_region_s")
-    line["roofline"] = pick(record["roofline"], "bound", "kernel", "achieved", "peak", "unit", "frac", "frac_of_best_copy")
+    line["roofline"] = pick(record["roofline"], "bound", "kernel", "achieved", "peak", "unit", "frac", "traffic", "frac_of_best_copy")
     line["kernels_avg_ms"] = {k: v["avg_ms"] for k, v in record["kernels"].items()}
 
     def short(d):
